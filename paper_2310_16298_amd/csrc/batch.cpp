@@ -170,6 +170,23 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       b->groups.back().k = k;
       return b->groups.size() - 1;
     };
+    // columns per lane and shares of the waves of the 2D time-blocked grids, by class
+    std::vector<int> columns(count, 0), share(count, 0);
+    std::map<std::pair<Picker, int>, std::vector<int32_t>> members;
+    for (int32_t i = 0; i < count; ++i)
+      if (plans[i]->rs.family == FAM_TB2D && plans[i]->rs.tb_auto)
+        members[{plans[i]->rs.pick_batch, plans[i]->rs.time_block}].push_back(i);
+    for (const auto& m : members) {
+      std::vector<const Resolved*> grids;
+      for (int32_t i : m.second) grids.push_back(&plans[i]->rs);
+      std::vector<int> sh;
+      int nc = 0;
+      rs2d_batch_cut(grids, &sh, &nc);
+      for (size_t k = 0; k < m.second.size(); ++k) {
+        columns[m.second[k]] = nc;
+        share[m.second[k]] = sh[k];
+      }
+    }
     for (int32_t i = 0; i < count; ++i) {
       const Resolved& rs = plans[i]->rs;
       const int T = rs.tb_auto ? rs.time_block : 1;
@@ -182,7 +199,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
         std::vector<KArgs> as(T + 1);
         bool ok = true;
         for (int sz = 1; sz <= T && ok; ++sz) {
-          ks[sz] = plan_kernel(rs, buf0[i], buf1[i], &as[sz], sz, rs.pick_batch);
+          ks[sz] = plan_kernel(rs, buf0[i], buf1[i], &as[sz], sz, rs.pick_batch, columns[i], share[i]);
           ok = ks[sz].launch && ks[sz].items >= 1;
         }
         if (ok) {

@@ -1,0 +1,8 @@
+// Register-streaming time-blocked 2D gather: F64 box stencils.
+#include "kernels_rs2d_inst.hpp"
+
+namespace stencil {
+
+template Kernel rs2d_of<double, true>(int R, int NC, int64_t items);
+
+}  // namespace stencil

@@ -1,38 +1,148 @@
-// Instantiations of the time-blocked 2D gather kernels.
+// Kernel choice of the time-blocked 2D gather.
+#include <algorithm>
 #include <type_traits>
 
+#include "kernels_rs2d.hpp"
 #include "kernels_tb2d.hpp"
 #include "launch.hpp"
 #include "plan.hpp"
 
 namespace stencil {
 
-// MANY: the grid is one of many in a batched launch, whose items fill the
-// chip without the small-grid tiles below
+// Work decomposition of the register-streaming kernel: strips of 64 NC
+// columns, chunks of rows.  A launch runs two waves per SIMD (kRsWaves = 2048 on
+// 256 CUs), each with an issue port of its own, so a grid alone is cut into
+// that many waves; a wave's time is its rows, 3/4 of the pipeline's fill
+// included, times the instructions of a row, and the NC with the shortest
+// time is taken.  8192^2 FP32 order-2 box, NC = 4: 1283 GStencil/s at two waves per
+// SIMD, 996 at one, 1212 at four.
+namespace {
+
+struct RsCut {
+  int64_t strips = 0, chunks = 0, ch = 0;
+  double wave = 0.0;  // issue slots of one wave
+};
+
+// waves_for: the waves the grid is cut into; `many`: chunks of 8 to 64 rows
+// (longer ones gain little and balance worse).
+RsCut rs_cut(const KArgs& a, int R, bool box, int es, int steps, int NC, int64_t waves_for, bool many) {
+  RsCut c;
+  KArgs b = a;
+  b.steps = steps;
+  const int cols = (64 - 2 * rs2d_halo_lanes(b, R, NC)) * NC;
+  c.strips = (a.d1 + cols - 1) / cols;
+  int64_t chunks = std::max<int64_t>(1, std::min<int64_t>(a.d0, waves_for / c.strips));
+  if (many) chunks = std::max((a.d0 + 63) / 64, std::min((a.d0 + 7) / 8, chunks));
+  c.ch = (a.d0 + chunks - 1) / chunks;
+  c.chunks = (a.d0 + c.ch - 1) / c.ch;
+  // per row and level: the FMAs, the moves of 2R halo columns (about three
+  // issue slots each), the loop's own
+  const int taps = box ? (2 * R + 1) * (2 * R + 1) : 4 * R + 1;
+  c.wave = (c.ch + 1.5 * R * steps) * (taps * NC + 3.0 * R * (es / 4) + 4);
+  return c;
+}
+
+bool rs_columns_ok(const KArgs& a, int NC, const RsCut& c) {
+  return NC <= a.d1 && c.strips * c.chunks <= (int64_t(1) << 30);
+}
+
+}  // namespace
+
+// The grids of one batch class (same type, order, shape and step count) share
+// one kernel, so one NC: the one with the shortest class time, its work over
+// the full chip or its longest wave.  A grid's share of the waves goes by its
+// bytes.
+void rs2d_batch_cut(const std::vector<const Resolved*>& grids, std::vector<int>* share, int* columns) {
+  double all = 0.0;
+  for (const Resolved* g : grids) all += (double)g->args.d0 * (double)g->args.d1;
+  share->clear();
+  for (const Resolved* g : grids)
+    share->push_back(std::max(1, (int)(kRsWaves * ((double)g->args.d0 * (double)g->args.d1 / all))));
+  *columns = 0;
+  double best = 0.0;
+  for (int NC = 1; NC <= 4; NC *= 2) {
+    double work = 0.0, longest = 0.0;
+    bool ok = true;
+    for (size_t k = 0; k < grids.size() && ok; ++k) {
+      const Resolved& g = *grids[k];
+      const RsCut c = rs_cut(g.args, g.info.radius, g.info.shape != STENCIL_STAR, g.info.dtype == STENCIL_F64 ? 8 : 4,
+                             g.time_block, NC, (*share)[k], true);
+      ok = rs_columns_ok(g.args, NC, c);
+      const double wave = c.wave + 1500.0;  // finding the grid, its weights, the first rows
+      work += wave * (double)(c.strips * c.chunks);
+      longest = std::max(longest, wave);
+    }
+    const double t = std::max(work / kRsWaves, longest);
+    if (!ok || (*columns && t >= best)) continue;
+    *columns = NC;
+    best = t;
+  }
+  if (*columns == 0) *columns = 1;
+}
+
+// Cuts the grid (MANY: for the NC in a.tiles0 and the share of the waves in
+// a.nchunks) and returns NC.
+template <typename T, int R, bool BOX, bool MANY>
+static int cut_rs2d(KArgs& a) {
+  const KArgs in = a;
+  int best = 0;
+  double best_time = 0.0;
+  for (int NC = 1; NC <= 4; NC *= 2) {
+    if (MANY && NC != in.tiles0) continue;
+    const int64_t waves_for = MANY ? in.nchunks : kRsWaves;
+    const RsCut c = rs_cut(in, R, BOX, (int)sizeof(T), in.steps, NC, waves_for, MANY);
+    const double waves = (double)(c.strips * c.chunks);
+    const double t = c.wave * std::max(1.0, waves / (double)waves_for);
+    if (!rs_columns_ok(in, NC, c) || (best && t >= best_time)) continue;
+    best = NC;
+    best_time = t;
+    a.tiles1 = (int32_t)c.strips;
+    a.chunk = (int32_t)c.ch;
+    a.nchunks = (int32_t)c.chunks;
+  }
+  return best;
+}
+
+// The LDS tiles (direct-to-LDS windows of 64 x 64, FP64 32 x 64) for a grid
+// alone that they suit better: orders 3 and 4 on grids in between, where the
+// pipeline's fill of 2 R steps rows is long against the chunks of a full
+// chip, and (FP64) its latency against 16-row tiles.  us per launch, LDS tiles
+// / register streaming: FP32 order-4 box 512^2 13.3 / 12.0, 1024^2 13.8 / 17.4,
+// 2048^2 27 / 37, 4096^2 81 / 94, 6144^2 184 / 174; order-4 star 700^2 11.9 / 10.6,
+// 1024^2 12.0 / 12.6, 1500^2 14.9 / 16.3, 2048^2 22.2 / 21.3; order-3 box 700^2 20.5 /
+// 19.0, 1024^2 20.6 / 23.4, 1500^2 34.9 / 35.2, 2500^2 69 / 62; FP64 order-4 star
+// 256^2 7.3 / 7.1, 512^2 7.1 / 8.2, 1024^2 11.7 / 11.9, 1500^2 17.5 / 16.0; order-4 box
+// 64^2 10.8 / 12.5, 512^2 9.9 / 21.5, 2048^2 53 / 68, 4096^2 190 / 172.
+template <typename T, int R, bool BOX>
+static bool lds_tiles_better(const KArgs& a) {
+  const int64_t pts = a.d0 * a.d1;
+  if constexpr (sizeof(T) == 4)
+    return R == 4 ? (BOX ? pts >= 450000 && pts < 32000000 : pts >= 800000 && pts < 3000000)
+                  : R == 3 && BOX && pts >= 800000 && pts < 2400000;
+  else
+    return R == 4 && (BOX ? pts < 10000000 : pts >= 100000 && pts < 1100000);
+}
+
+// MANY: the grid is one of many in a batched launch, whose items fill the chip
 template <typename T, int R, bool BOX, bool MANY = false>
 static Kernel pick_tb2d(KArgs& a, int32_t chunk) {
   // a launch of one step (the remainder of a run): the one-step gather
   if (a.steps <= 1) return find_gather2d(std::is_same<T, double>::value ? STENCIL_F64 : STENCIL_F32, R, BOX)(a, chunk);
-  if (tb2d_fast<T>(a) && a.zeros != nullptr) {
-    int TM = tb2d_dma_rows<T>();
-    a.tiles1 = (int32_t)((a.d1 + 63) / 64);
-    // FP64 grids of fewer tiles than CUs (launch-bound: 512^2 has 128) take
-    // 16-row tiles, twice the workgroups at the cost of more halo rows
-    // (MI355X, 512^2 FP64 five-point star, 8 steps per launch: see below);
-    // not in a batch, where their halo rows cost without the occupancy gain
-    const bool small =
-        !MANY && !std::is_same<T, float>::value && (int64_t)((a.d0 + TM - 1) / TM) * a.tiles1 < 256;
-    if (small) TM = kTbSmallRows;
-    a.tiles0 = (int32_t)((a.d0 + TM - 1) / TM);
-    const int64_t items = (int64_t)a.tiles0 * a.tiles1;
-    Kernel k;
-    if constexpr (std::is_same<T, float>::value) k = BOX ? tb2d_dma_box(R, a.steps, items) : tb2d_dma_star(R, a.steps, items);
-    else k = tb2d_dma_f64(BOX, R, a.steps, items, small);
-    if (k.launch) return k;
+  if constexpr (!MANY && tb2d_dma_built<T>(R, BOX)) {
+    if (tb2d_fast<T>(a) && a.zeros != nullptr && lds_tiles_better<T, R, BOX>(a)) {
+      int TM = TbDmaShape<T, R, 2>::TM;
+      a.tiles1 = (int32_t)((a.d1 + 63) / 64);
+      // FP64 grids of fewer tiles than CUs (launch-bound: 512^2 has 128) take
+      // 16-row tiles, twice the workgroups at the cost of more halo rows
+      const bool small = !std::is_same<T, float>::value && (int64_t)((a.d0 + TM - 1) / TM) * a.tiles1 < 256;
+      if (small) TM = kTbSmallRows;
+      a.tiles0 = (int32_t)((a.d0 + TM - 1) / TM);
+      return tb2d_dma<T, BOX>(R, a.steps, (int64_t)a.tiles0 * a.tiles1, small);
+    }
   }
-  const int64_t items = tb2d_items<T>(a);
-  if (tb2d_fast<T>(a)) return kernel_of<tb2d_kernel<T, R, BOX, true>, tb2d_batch<T, R, BOX, true>>(items);
-  return kernel_of<tb2d_kernel<T, R, BOX, false>, tb2d_batch<T, R, BOX, false>>(items);
+  const int NC = cut_rs2d<T, R, BOX, MANY>(a);
+  if (NC == 0) return Kernel{};
+  return rs2d_of<T, BOX>(R, NC, ((int64_t)a.tiles1 * a.nchunks + 3) / 4);
 }
 
 template <typename T, bool BOX, bool MANY>
@@ -55,11 +165,6 @@ static Picker find(int dtype, int R, bool box) {
 Picker find_tb2d(int dtype, int R, bool box) { return find<false>(dtype, R, box); }
 Picker find_tb2d_batch(int dtype, int R, bool box) { return find<true>(dtype, R, box); }
 
-int tb2d_max_steps(int dtype, int R) {
-  const int hmax = dtype == STENCIL_F64 ? TbShape<double>::HMAX : TbShape<float>::HMAX;
-  int t = 1;
-  while (tb_halo(R, t + 1) <= hmax) ++t;
-  return t;
-}
+int tb2d_max_steps(int dtype, int R) { return dtype == STENCIL_F64 ? rs2d_steps<double>(R) : rs2d_steps<float>(R); }
 
 }  // namespace stencil

@@ -67,4 +67,14 @@ inline Kernel kernel_of(int64_t items) {
   return k;
 }
 
+// A kernel that is only launched for one grid.
+template <auto KS>
+inline Kernel kernel_of(int64_t items) {
+  Kernel k;
+  k.launch = launch_single<KS>;
+  k.single_id = reinterpret_cast<const void*>(KS);
+  k.items = items;
+  return k;
+}
+
 }  // namespace stencil

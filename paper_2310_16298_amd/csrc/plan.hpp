@@ -83,7 +83,11 @@ Picker find_mfma3d(int dtype, int R, bool box);
 Picker find_mfma3d_b4(int R, bool box);  // FP32 n = 4 blocks: stars, 27-point box
 Picker find_split3d(int kind, int R, bool box, bool hybrid);  // hybrid: stars, lines along j and k on MFMA
 Picker find_tb2d(int dtype, int R, bool box);
-Picker find_tb2d_batch(int dtype, int R, bool box);  // among many grids: FP64 tiles of full height
+// Among many grids: reads the columns per lane and the grid's share of the
+// waves, which rs2d_batch_cut chooses, from a.tiles0 and a.nchunks.
+Picker find_tb2d_batch(int dtype, int R, bool box);
+void rs2d_batch_cut(const std::vector<const Resolved*>& grids, std::vector<int>* share, int* columns);
+constexpr int kRsWaves = 2048;  // waves of a full launch of the register-streaming kernel
 Picker find_tb3d(int dtype, int R, bool box);  // two steps per launch
 Picker find_tb3d_batch(int dtype, int R, bool box);  // among many grids: the streaming form or none
 Picker find_tbm2d(int R);  // FP32 2D box outer products, two steps per launch
