@@ -93,9 +93,9 @@ typedef enum {
                                    at the nonzero-tap limit of the GENERAL gather, past which the
                                    all-tap gather runs at about that cost) against
                                    12910 + 1530 L (2r+4)/12 for L lines), GATHER otherwise; 2D
-                                   grids whose column extent is not
-                                   a multiple of 4, or at most 64 (stars, the F64 9-point box),
-                                   take MFMA;
+                                   grids of at most 64 columns (stars, the F64 9-point box), or
+                                   of at most 68 and not a multiple of 4, take MFMA, and so do
+                                   GENERAL ones of any other extent not a multiple of 4;
                                    stencil_plan_info reports the choice */
   STENCIL_PATH_GATHER = 1,      /* gather-form vector kernel, Eq. (1) */
   STENCIL_PATH_MFMA = 2,        /* outer-product form on MFMA in the grid dtype (FP32 or FP64) */
@@ -137,8 +137,8 @@ typedef struct {
                            extent */
   int32_t time_block;   /* steps fused per launch (time blocking; the temporal reuse Section 6
                            leaves to future work): 1 = one step per launch; T > 1: each launch
-                           advances T steps on overlapped tiles held in LDS (halo r*T), cutting HBM
-                           traffic per point-step about T-fold.  Built for 2D grids on the GATHER
+                           advances T steps on overlapped pieces (halo r*T) held in registers or
+                           LDS, cutting HBM traffic per point-step about T-fold.  Built for 2D grids on the GATHER
                            path (AUTO resolves to it), and T = 2 on the MFMA path for F32 BOX grids
                            whose column extent is a multiple of 4 with block_n, reg_rows and
                            tile_width left at 0 / 4 / 16 / 256 (n = 4 outer products at both levels;
@@ -151,8 +151,8 @@ typedef struct {
                            aligned buffers, else stencil_run_steps returns EINVAL); else
                            EUNSUPPORTED.  0 = library choice:
                            one step per launch, except that path AUTO on 2D STAR / BOX grids
-                           whose column extent is a multiple of 4 (the F32 order-4 box: and
-                           more than 64), with
+                           whose column extent is a multiple of 4 or more than 68 (the F32
+                           order-4 box: more than 64), with
                            lines, block_n, chunk, reg_rows and tile_width all 0, takes the
                            time-blocked gather with T measured fastest on MI355X (r = 1..4,
                            F32 stars 8 / 4 / 4 / 3, boxes 8 / 4 / 4 / 2; F64 stars 8 / 4 / 2 /

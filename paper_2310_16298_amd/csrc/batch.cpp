@@ -170,12 +170,14 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       b->groups.back().k = k;
       return b->groups.size() - 1;
     };
-    // columns per lane and shares of the waves of the 2D time-blocked grids, by class
+    // columns per lane and shares of the waves of the 2D gathers, by class
     std::vector<int> columns(count, 0), share(count, 0);
     std::map<std::pair<Picker, int>, std::vector<int32_t>> members;
-    for (int32_t i = 0; i < count; ++i)
-      if (plans[i]->rs.family == FAM_TB2D && plans[i]->rs.tb_auto)
-        members[{plans[i]->rs.pick_batch, plans[i]->rs.time_block}].push_back(i);
+    for (int32_t i = 0; i < count; ++i) {
+      const Resolved& rs = plans[i]->rs;
+      if (rs.family == FAM_TB2D) members[{rs.pick_batch, rs.time_block}].push_back(i);
+      if (rs.family == FAM_GATHER2D) members[{rs.pick, 1}].push_back(i);
+    }
     for (const auto& m : members) {
       std::vector<const Resolved*> grids;
       for (int32_t i : m.second) grids.push_back(&plans[i]->rs);
@@ -227,7 +229,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       }
       if (placed) continue;
       KArgs a;
-      const Kernel k = plan_kernel(rs, buf0[i], buf1[i], &a);
+      const Kernel k = plan_kernel(rs, buf0[i], buf1[i], &a, 1, nullptr, columns[i], share[i]);
       if (!k.launch || k.items < 1) {
         delete b;
         return STENCIL_EINTERNAL;

@@ -31,6 +31,8 @@
 // 232 us (1.07 GB: 4.6 TB/s), boxes (8 / 4) 615 / 506 -> 252 / 309 us.
 #pragma once
 
+#include <algorithm>
+
 #include "device_common.hpp"
 #include "launch.hpp"
 
@@ -138,7 +140,8 @@ __host__ __device__ inline int rs2d_halo_lanes(const KArgs& a, int R, int NC) {
 // 2^31): r < M as unsigned says that row r lies in the grid.
 template <typename T, int R, bool BOX, int TS, int NC>
 struct RsWave {
-  static constexpr int W = 2 * R + 1, U = 2;
+  static constexpr int W = 2 * R + 1;
+  static constexpr int U = TS == 1 ? 4 : 2;  // rows loaded ahead
   T acc[TS][2 * R][NC];  // level t + 1: its unfinished output rows, oldest first
   // The weights stay in registers for the whole walk.  FP32: vector registers
   // (a scalar operand would keep a second wave from issuing beside this one),
@@ -324,8 +327,9 @@ struct RsWave {
   // fill the pipeline level by level, then stream the chunk's ch rows
   template <int L, int MODE>
   __device__ __forceinline__ void fill(int steps, int ch, T (*nx)[NC]) {
+    static_assert(TS == 1 || 2 * R % U == 0, "whole rounds of rows");
     const bool last = L == TS || L == steps;
-    rows<L, MODE>(last ? 2 * R + (ch + U - 1) / U * U : 2 * R, last ? 2 * R : 0x40000000, last ? ch : 0, nx);
+    rows<L, MODE>(last ? (2 * R + ch + U - 1) / U * U : 2 * R, last ? 2 * R : 0x40000000, last ? ch : 0, nx);
     if constexpr (L < TS) {
       if (!last) fill<L + 1, MODE>(steps, ch, nx);
     }
@@ -406,6 +410,43 @@ __global__ __launch_bounds__(256) void rs2d_batch(BatchArgs b) {
   for_each_batch_item(b, [&](const KArgs& x, int id) { rs2d_item<T, R, BOX, TS, NC>(x, id); });
 }
 
+// Work decomposition of the register-streaming kernel: strips of 64 NC
+// columns, chunks of rows.  A launch runs two waves per SIMD (kRsWaves = 2048 on
+// 256 CUs), each with an issue port of its own, so a grid alone is cut into
+// that many waves; a wave's time is its rows, 3/4 of the pipeline's fill
+// included, times the instructions of a row, and the NC with the shortest
+// time is taken.  8192^2 FP32 order-2 box, NC = 4: 1283 GStencil/s at two waves per
+// SIMD, 996 at one, 1212 at four.
+constexpr int kRsWaves = 2048;  // two per SIMD
+
+struct RsCut {
+  int64_t strips = 0, chunks = 0, ch = 0;
+  double wave = 0.0;  // issue slots of one wave
+};
+
+// waves_for: the waves the grid is cut into; `many`: chunks of 8 to 64 rows
+// (longer ones gain little and balance worse).
+inline RsCut rs_cut(const KArgs& a, int R, bool box, int es, int steps, int NC, int64_t waves_for, bool many) {
+  RsCut c;
+  KArgs b = a;
+  b.steps = steps;
+  const int cols = (64 - 2 * rs2d_halo_lanes(b, R, NC)) * NC;
+  c.strips = (a.d1 + cols - 1) / cols;
+  int64_t chunks = std::max<int64_t>(1, std::min<int64_t>(a.d0, waves_for / c.strips));
+  if (many) chunks = std::max((a.d0 + 63) / 64, std::min((a.d0 + 7) / 8, chunks));
+  c.ch = (a.d0 + chunks - 1) / chunks;
+  c.chunks = (a.d0 + c.ch - 1) / c.ch;
+  // per row and level: the FMAs, the moves of 2R halo columns (about three
+  // issue slots each), the loop's own
+  const int taps = box ? (2 * R + 1) * (2 * R + 1) : 4 * R + 1;
+  c.wave = (c.ch + 1.5 * R * steps) * (taps * NC + 3.0 * R * (es / 4) + 4);
+  return c;
+}
+
+inline bool rs_columns_ok(const KArgs& a, int NC, const RsCut& c) {
+  return NC <= a.d1 && c.strips * c.chunks <= (int64_t(1) << 30);
+}
+
 // Levels built per order: the largest step count of a time-blocked launch.
 template <typename T>
 constexpr int rs2d_steps(int R) {
@@ -415,5 +456,8 @@ constexpr int rs2d_steps(int R) {
 // The kernel for order R and NC columns per lane.
 template <typename T, bool BOX>
 Kernel rs2d_of(int R, int NC, int64_t items);
+// The same walk with one step (NC = 2).
+template <typename T, bool BOX>
+Kernel rs2d_one(int R, int64_t items);
 
 }  // namespace stencil

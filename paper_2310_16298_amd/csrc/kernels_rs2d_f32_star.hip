@@ -1,8 +1,9 @@
-// Register-streaming time-blocked 2D gather: F32 star stencils.
+// Register-streaming 2D gather: F32 star stencils.
 #include "kernels_rs2d_inst.hpp"
 
 namespace stencil {
 
 template Kernel rs2d_of<float, false>(int R, int NC, int64_t items);
+template Kernel rs2d_one<float, false>(int R, int64_t items);
 
 }  // namespace stencil

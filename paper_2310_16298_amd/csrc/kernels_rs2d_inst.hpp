@@ -27,4 +27,15 @@ Kernel rs2d_of(int R, int NC, int64_t items) {
   return Kernel{};
 }
 
+template <typename T, bool BOX>
+Kernel rs2d_one(int R, int64_t items) {
+  switch (R) {
+    case 1: return kernel_of<rs2d_kernel<T, 1, BOX, 1, 2>, rs2d_batch<T, 1, BOX, 1, 2>>(items);
+    case 2: return kernel_of<rs2d_kernel<T, 2, BOX, 1, 2>, rs2d_batch<T, 2, BOX, 1, 2>>(items);
+    case 3: return kernel_of<rs2d_kernel<T, 3, BOX, 1, 2>, rs2d_batch<T, 3, BOX, 1, 2>>(items);
+    case 4: return kernel_of<rs2d_kernel<T, 4, BOX, 1, 2>, rs2d_batch<T, 4, BOX, 1, 2>>(items);
+  }
+  return Kernel{};
+}
+
 }  // namespace stencil

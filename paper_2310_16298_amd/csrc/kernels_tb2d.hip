@@ -9,45 +9,6 @@
 
 namespace stencil {
 
-// Work decomposition of the register-streaming kernel: strips of 64 NC
-// columns, chunks of rows.  A launch runs two waves per SIMD (kRsWaves = 2048 on
-// 256 CUs), each with an issue port of its own, so a grid alone is cut into
-// that many waves; a wave's time is its rows, 3/4 of the pipeline's fill
-// included, times the instructions of a row, and the NC with the shortest
-// time is taken.  8192^2 FP32 order-2 box, NC = 4: 1283 GStencil/s at two waves per
-// SIMD, 996 at one, 1212 at four.
-namespace {
-
-struct RsCut {
-  int64_t strips = 0, chunks = 0, ch = 0;
-  double wave = 0.0;  // issue slots of one wave
-};
-
-// waves_for: the waves the grid is cut into; `many`: chunks of 8 to 64 rows
-// (longer ones gain little and balance worse).
-RsCut rs_cut(const KArgs& a, int R, bool box, int es, int steps, int NC, int64_t waves_for, bool many) {
-  RsCut c;
-  KArgs b = a;
-  b.steps = steps;
-  const int cols = (64 - 2 * rs2d_halo_lanes(b, R, NC)) * NC;
-  c.strips = (a.d1 + cols - 1) / cols;
-  int64_t chunks = std::max<int64_t>(1, std::min<int64_t>(a.d0, waves_for / c.strips));
-  if (many) chunks = std::max((a.d0 + 63) / 64, std::min((a.d0 + 7) / 8, chunks));
-  c.ch = (a.d0 + chunks - 1) / chunks;
-  c.chunks = (a.d0 + c.ch - 1) / c.ch;
-  // per row and level: the FMAs, the moves of 2R halo columns (about three
-  // issue slots each), the loop's own
-  const int taps = box ? (2 * R + 1) * (2 * R + 1) : 4 * R + 1;
-  c.wave = (c.ch + 1.5 * R * steps) * (taps * NC + 3.0 * R * (es / 4) + 4);
-  return c;
-}
-
-bool rs_columns_ok(const KArgs& a, int NC, const RsCut& c) {
-  return NC <= a.d1 && c.strips * c.chunks <= (int64_t(1) << 30);
-}
-
-}  // namespace
-
 // The grids of one batch class (same type, order, shape and step count) share
 // one kernel, so one NC: the one with the shortest class time, its work over
 // the full chip or its longest wave.  A grid's share of the waves goes by its

@@ -433,8 +433,7 @@ int resolve_plan(const stencil_desc_t* desc, Resolved* rs, bool pack) {
     // outgrows the memory traffic -- FP32 boxes of radius >= 3 (2D and 3D)
     // and 2D GENERAL line covers -- and the gather kernel elsewhere (stars and
     // small boxes stay HBM-bound, where the gather kernel ties or wins; the
-    // FP64 matrix rate equals the FP64 vector rate).  2D extents whose column
-    // count is not a multiple of 4 (no direct-to-LDS windows): outer products.
+    // FP64 matrix rate equals the FP64 vector rate).
     const bool f32 = d.dtype == STENCIL_F32;
     if (nd == 3) {
       // Stars of radius 4 stay on the gather kernel: FP32 ahead by 4 % at
@@ -487,10 +486,17 @@ int resolve_plan(const stencil_desc_t* desc, Resolved* rs, bool pack) {
         const int n_eff = std::min(in.taps, kSparseMax[0][R]);
         if (12 * 403 * n_eff < 12 * 620 + 1530 * L * (4 + 2 * R)) heavy = false;
       }
-      path = dma_cols && !heavy && !narrow ? STENCIL_PATH_GATHER : STENCIL_PATH_MFMA;
-      // Time blocking: on grids that take direct-to-LDS windows, the
-      // time-blocked gather with the step count measured fastest on MI355X
-      // (512^2, 2048^2 and 8192^2, periodic) beats every one-step plan.  On
+      // Column extents that are not a multiple of 4 cannot take direct-to-LDS
+      // windows; the register-streaming gather does not need them and beats the
+      // outer products' register-staged windows by 2-5x (1021 x 1531, one step: FP32
+      // stars 14-15 us against 5.5-6.9, boxes r = 3, 4 18-19 against 8.8-11.8, FP64
+      // boxes 17-34 against 6-18; 75^2 17-22 against 3.6-7.5).  Up to 68 columns
+      // such grids keep the outer products, the choice their callers know.
+      const bool ragged = !dma_cols && d.dims[1] > 68 && !general;
+      path = (dma_cols && !heavy && !narrow) || ragged ? STENCIL_PATH_GATHER : STENCIL_PATH_MFMA;
+      // Time blocking: the time-blocked gather with the step count measured
+      // fastest on MI355X (512^2, 2048^2 and 8192^2, periodic) beats every
+      // one-step plan.  On
       // narrow grids too (10 steps, alone: 32^2, 48^2, 32 x 128 and 64^2 take
       // 24-60 us against 50-108 us for the best one-step plan; batches of 64^2
       // grids run 1.6-2.1x faster), except the FP32 box of order 4, which
@@ -503,7 +509,7 @@ int resolve_plan(const stencil_desc_t* desc, Resolved* rs, bool pack) {
       static const int kAutoTimeBlock[2][2][5] = {{{0, 8, 4, 4, 3}, {0, 8, 4, 4, 2}},   // F32 star, box
                                                   {{0, 8, 4, 2, 2}, {0, 8, 4, 0, 0}}};  // F64 star, box
       const bool tb_cols = d.dims[1] > 64 || !(f32 && box && R == 4);
-      if (!general && dma_cols && tb_cols && d.time_block == 0 && d.lines == STENCIL_LINES_AUTO &&
+      if (!general && (dma_cols || ragged) && tb_cols && d.time_block == 0 && d.lines == STENCIL_LINES_AUTO &&
           d.block_n == 0 && d.chunk == 0 && d.reg_rows == 0 && d.tile_width == 0) {
         const int t = kAutoTimeBlock[f32 ? 0 : 1][box ? 1 : 0][R];
         if (t > 1) {

@@ -87,7 +87,6 @@ Picker find_tb2d(int dtype, int R, bool box);
 // waves, which rs2d_batch_cut chooses, from a.tiles0 and a.nchunks.
 Picker find_tb2d_batch(int dtype, int R, bool box);
 void rs2d_batch_cut(const std::vector<const Resolved*>& grids, std::vector<int>* share, int* columns);
-constexpr int kRsWaves = 2048;  // waves of a full launch of the register-streaming kernel
 Picker find_tb3d(int dtype, int R, bool box);  // two steps per launch
 Picker find_tb3d_batch(int dtype, int R, bool box);  // among many grids: the streaming form or none
 Picker find_tbm2d(int R);  // FP32 2D box outer products, two steps per launch

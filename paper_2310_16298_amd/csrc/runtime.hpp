@@ -119,7 +119,7 @@ inline stencil_status_t check_device(int device) {
 
 // The resolved plan's args with the two buffers and the launch's step count
 // filled in, its kernel picked (by `pick`, else the plan's own picker) and the
-// decomposition applied.  columns / share: a 2D batch picker's cut.
+// decomposition applied.  columns / share: the cut of a 2D gather in a batch.
 inline Kernel plan_kernel(const Resolved& rs, const void* in, void* out, KArgs* a, int fused = 1,
                           Picker pick = nullptr, int columns = 0, int share = 0) {
   *a = rs.args;
