@@ -84,7 +84,8 @@ typedef enum { STENCIL_F32 = 0, STENCIL_F64 = 1 } stencil_dtype_t;
 
 typedef enum {
   STENCIL_PATH_AUTO = 0,        /* library picks, from measurements on MI355X: MFMA for F32 boxes of
-                                   order >= 3 (2D and 3D; 3D GENERAL stencils with at most 88 / 128
+                                   order >= 3 (2D and 3D; 3D boxes of up to about 256^3 points
+                                   and 3D GENERAL stencils with at most 88 / 128
                                    nonzero taps at order 3 / 4 take GATHER), F64 3D stars of order
                                    4 and 2D GENERAL
                                    stencils (FP32 grids wider than 64 columns: the line cover or
@@ -131,9 +132,9 @@ typedef struct {
                            instructions (F64, 2D orthogonal stars, 3D boxes up to order 2); any
                            other resolved block edge: EUNSUPPORTED; ignored by the GATHER path */
   int32_t chunk;        /* output rows (2D) or i-planes (3D) per workgroup work item: 0 = library
-                           choice (on the 3D GATHER path a grid that fits the LDS with its halo,
-                           8^3 or 16^3 say, is then one work item computed whole by one
-                           workgroup); rounded up to the kernel's row block and clipped to the
+                           choice (in a batch, a grid on the 3D GATHER path that fits the LDS with
+                           its halo, 8^3 or 16^3 say, is then one work item computed whole by
+                           one workgroup); rounded up to the kernel's row block and clipped to the
                            extent */
   int32_t time_block;   /* steps fused per launch (time blocking; the temporal reuse Section 6
                            leaves to future work): 1 = one step per launch; T > 1: each launch

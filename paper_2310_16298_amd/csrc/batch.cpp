@@ -171,7 +171,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       return b->groups.size() - 1;
     };
     // columns per lane and shares of the waves of the 2D gathers, by class
-    std::vector<int> columns(count, 0), share(count, 0);
+    std::vector<int> columns(count, 0), share(count, 1);
     std::map<std::pair<Picker, int>, std::vector<int32_t>> members;
     for (int32_t i = 0; i < count; ++i) {
       const Resolved& rs = plans[i]->rs;

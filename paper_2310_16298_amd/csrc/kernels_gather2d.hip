@@ -32,9 +32,8 @@ template <typename T, int R, bool BOX>
 static Kernel pick_gather2d(KArgs& a, int32_t chunk) {
   constexpr int TN = Gather2DDma<T>::TN;
   if (row_walk_better<T, R, BOX>(a)) {
-    // in a batch or a server a.nchunks holds the grid's share of the waves
-    const bool many = a.nchunks > 0;
-    RsCut c = rs_cut(a, R, BOX, (int)sizeof(T), 1, 2, many ? a.nchunks : kRsWaves, many);
+    const bool many = a.share > 0;
+    RsCut c = rs_cut(a, R, BOX, (int)sizeof(T), 1, 2, many ? a.share : kRsWaves, many);
     if (chunk > 0) {
       c.ch = chunk < a.d0 ? chunk : a.d0;
       c.chunks = (a.d0 + c.ch - 1) / c.ch;

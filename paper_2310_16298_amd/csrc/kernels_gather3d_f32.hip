@@ -1,5 +1,6 @@
 // Instantiations of the 3D gather-form baseline kernel, float grids.
 #include "kernels_3d.hpp"
+#include "kernels_rows3d.hpp"
 #include "launch.hpp"
 #include "plan.hpp"
 
@@ -7,8 +8,14 @@ namespace stencil {
 
 template <int R, bool BOX>
 static Kernel pick_gather3d(KArgs& a, int32_t chunk) {
-  const Kernel whole = whole3d_kernel<float, R, BOX>(a, chunk);  // small grids
-  if (whole.launch) return whole;
+  if (a.share > 0) {  // small grids among many: a workgroup each
+    const Kernel whole = whole3d_kernel<float, R, BOX>(a, chunk);
+    if (whole.launch) return whole;
+  }
+  if (chunk == 0) {
+    const Rows3DCut c = rows3d_best(a, R, BOX, (int)sizeof(float));
+    if (c.NC && rows3d_better<float, R, BOX>(a, c)) return rows3d_kernel_for<float, R, BOX>(a, c);
+  }
   if (dma3d_ok<float>(a)) return kernel3d<gather3d_kernel<float, R, BOX, true>, gather3d_batch<float, R, BOX, true>>(a, R, chunk);
   return kernel3d<gather3d_kernel<float, R, BOX, false>, gather3d_batch<float, R, BOX, false>>(a, R, chunk);
 }

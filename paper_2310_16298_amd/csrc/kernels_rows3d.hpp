@@ -1,0 +1,386 @@
+// 3D gather on register rows: one step, no LDS, no alignment or size demands.
+//
+// A wave computes J rows of one output plane over a strip of 64 NC columns
+// (lane l: columns NC l .. NC l + NC - 1).  It reads, plane by plane, the J + 2R
+// input rows around them (a star's planes other than its own: the J rows), takes
+// the k neighbours of a row from the lanes beside it by DPP shifts, and adds
+// the taps in the order of the tiled gather (planes, then j, then k ascending; a
+// star's centre plane: the j arm, then the k arm), so the results agree bit for
+// bit.  Rows that several waves read come from the caches: the four waves of a
+// workgroup take neighbouring row groups, an XCD a contiguous range of planes.
+// Strips overlap by the R columns that go stale on each side.
+//
+// What bounds it: the FMAs for boxes from order 2, the caches below that.  Against
+// the plane-ring kernel, whose chunks of at least 4R planes leave a small
+// grid a handful of workgroups and whose ragged windows are staged without
+// overlap (us a step, zero halo): 33^3 FP32 order-4 box 364 -> 14, order-1 star 22 ->
+// 3.5; 71^3 FP64 order-3 box 211 -> 19; 150^3 FP64 order-4 box 838 -> 177; 203 x 150 x 177
+// FP32 order-2 star 63 -> 16, FP64 27-point box 49 -> 21; 256^3 boxes FP32 order 2..4
+// 100 / 426 / 810 -> 69 / 167 / 344 (outer products 97 / 237 / 432), FP64 163 / 456 / 1383 ->
+// 111 / 231 / 504.
+#pragma once
+
+#include "dma3d.hpp"
+#include "kernels_rs2d.hpp"
+
+namespace stencil {
+
+template <typename T, int R, bool BOX, int NC, int J>
+struct Rows3D {
+  static constexpr int W = 2 * R + 1, XR = J + 2 * R;
+  T acc[J][NC];
+  ConstPtr<T> c;
+  const T* in;
+  uint32_t wcol;          // the lane's first column, wrapped / clamped into the row
+  uint32_t N, plane;      // columns; elements of a plane
+  uint32_t roff[XR];      // element offset of input row x in its plane (wrapped / clamped)
+  bool rok[XR];           // row x lies in the grid (periodic: always)
+  bool ok[NC];            // column e lies in the grid (periodic: always)
+  bool periodic;
+
+  template <int MODE>
+  __device__ __forceinline__ void load_row(const T* pl, int x, T* v) {
+    const T* src = pl + roff[x];
+    if constexpr (MODE < 2) {
+      const RsPack<T, NC> p = *reinterpret_cast<const RsPack<T, NC>*>(src + wcol);
+#pragma unroll
+      for (int e = 0; e < NC; ++e) v[e] = p.v[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < NC; ++e) v[e] = src[wcol + e < N ? wcol + e : (periodic ? wcol + e - N : 0u)];
+    }
+  }
+
+  // zero halo: what lies outside the grid
+  template <int MODE>
+  __device__ __forceinline__ void mask(int x, T* v) {
+    if constexpr (MODE > 0) {
+#pragma unroll
+      for (int e = 0; e < NC; ++e) v[e] = rok[x] && ok[e] ? v[e] : T(0);
+    }
+  }
+
+  // columns col - R .. col + NC - 1 + R of a row
+  __device__ __forceinline__ void widen(const T* v, T* e) {
+    constexpr int HL = (R + NC - 1) / NC;
+    T s[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) e[R + k] = s[k] = v[k];
+#pragma unroll
+    for (int h = 0; h < HL; ++h)
+#pragma unroll
+      for (int k = NC - 1; k >= 0; --k) {
+        const int at = k - NC * (h + 1);
+        if (at < -R) continue;
+        s[k] = rs_shift<true>(s[k]);
+        e[R + at] = s[k];
+      }
+#pragma unroll
+    for (int k = 0; k < NC; ++k) s[k] = v[k];
+#pragma unroll
+    for (int h = 0; h < HL; ++h)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        const int at = k + NC * (h + 1);
+        if (at > NC - 1 + R) continue;
+        s[k] = rs_shift<false>(s[k]);
+        e[R + at] = s[k];
+      }
+  }
+
+  template <int MODE>
+  __device__ __forceinline__ void load_plane(const T* pl, T (*v)[NC]) {
+#pragma unroll
+    for (int x = 0; x < XR; ++x) load_row<MODE>(pl, x, v[x]);
+  }
+
+  // box: the rows v of coefficient plane a
+  template <int MODE>
+  __device__ __forceinline__ void box_plane(int a, T (*v)[NC]) {
+    T w[W * W];
+#pragma unroll
+    for (int i = 0; i < W * W; ++i) {
+      w[i] = c[a * W * W + i];
+      if (sizeof(T) == 4) asm("" : "+v"(w[i]));  // a scalar operand would halve the FP32 issue rate
+    }
+#pragma unroll
+    for (int x = 0; x < XR; ++x) {
+      mask<MODE>(x, v[x]);
+      T e[2 * R + NC];
+      widen(v[x], e);
+#pragma unroll
+      for (int p = 0; p < J; ++p) {
+        const int b = x - p;
+        if (b < 0 || b > 2 * R) continue;
+#pragma unroll
+        for (int cc = 0; cc < W; ++cc)
+#pragma unroll
+          for (int k = 0; k < NC; ++k) acc[p][k] = rs_fma(w[b * W + cc], e[cc + k], acc[p][k]);
+      }
+    }
+  }
+
+  // in-plane arms of a star
+  template <int MODE>
+  __device__ __forceinline__ void star_centre(T (*v)[NC]) {
+#pragma unroll
+    for (int x = 0; x < XR; ++x) {
+      mask<MODE>(x, v[x]);
+#pragma unroll
+      for (int p = 0; p < J; ++p) {
+        const int b = x - p;
+        if (b < 0 || b > 2 * R) continue;
+        const T w = c[(R * W + b) * W + R];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) acc[p][k] = rs_fma(w, v[x][k], acc[p][k]);
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < J; ++p) {
+      T e[2 * R + NC];
+      widen(v[p + R], e);
+#pragma unroll
+      for (int cc = 0; cc < W; ++cc) {
+        if (cc == R) continue;
+        const T w = c[(R * W + R) * W + cc];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) acc[p][k] = rs_fma(w, e[cc + k], acc[p][k]);
+      }
+    }
+  }
+
+  // plane o + d of the input, nullptr outside a zero-halo grid
+  __device__ __forceinline__ const T* plane_at(int64_t o, int d, int64_t Ni) {
+    int64_t g = o + d;
+    if (g < 0 || g >= Ni) {
+      if (!periodic) return nullptr;
+      g %= Ni;
+      if (g < 0) g += Ni;
+    }
+    return in + g * (int64_t)plane;
+  }
+
+  template <int MODE>
+  __device__ __forceinline__ void point(int64_t o, int64_t Ni) {
+#pragma unroll
+    for (int p = 0; p < J; ++p)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) acc[p][k] = T(0);
+    const T* own = plane_at(o, 0, Ni);
+    if constexpr (BOX) {
+      // two planes' rows in turn: one is loaded while the other is added; a
+      // plane outside the grid is read as the own one and skipped
+      T va[XR][NC], vb[XR][NC];
+      const T* pa = plane_at(o, -R, Ni);
+      load_plane<MODE>(pa ? pa : own, va);
+#pragma unroll 1
+      for (int a = 0; a < W; a += 2) {
+        const T* pb = a + 1 < W ? plane_at(o, a + 1 - R, Ni) : nullptr;
+        load_plane<MODE>(pb ? pb : own, vb);
+        if (pa) box_plane<MODE>(a, va);
+        if (a + 1 >= W) break;
+        pa = plane_at(o, a + 2 - R, Ni);  // a + 2 < W: W is odd
+        load_plane<MODE>(pa ? pa : own, va);
+        if (pb) box_plane<MODE>(a + 1, vb);
+      }
+    } else {
+      T v[XR][NC], u[W][J][NC];
+      load_plane<MODE>(own, v);
+      const T* pl[W];
+#pragma unroll
+      for (int a = 0; a < W; ++a) {
+        if (a == R) continue;
+        pl[a] = plane_at(o, a - R, Ni);
+#pragma unroll
+        for (int p = 0; p < J; ++p) load_row<MODE>(pl[a] ? pl[a] : own, p + R, u[a][p]);
+      }
+#pragma unroll
+      for (int a = 0; a < W; ++a) {
+        if (a == R) {
+          star_centre<MODE>(v);
+          continue;
+        }
+        const T w = pl[a] ? c[(a * W + R) * W + R] : T(0);
+#pragma unroll
+        for (int p = 0; p < J; ++p) {
+          mask<MODE>(p + R, u[a][p]);
+#pragma unroll
+          for (int k = 0; k < NC; ++k) acc[p][k] = pl[a] ? rs_fma(w, u[a][p][k], acc[p][k]) : acc[p][k];
+        }
+      }
+    }
+  }
+};
+
+// Work decomposition: a.tiles0 row groups, a.tiles1 strips per plane; pieces
+// are numbered row group fastest, then strip, then plane; an item is four.
+template <typename T, int R, bool BOX, int NC, int J>
+__device__ __forceinline__ void rows3d_item(const KArgs& a, int item) {
+  typedef Rows3D<T, R, BOX, NC, J> S;
+  const int piece = __builtin_amdgcn_readfirstlane(item * 4 + (int)(threadIdx.x >> 6));
+  const int per_plane = a.tiles0 * a.tiles1;
+  const int o = piece / per_plane;
+  if (o >= a.d0) return;
+  const int rest = piece - o * per_plane;
+  const int si = rest / a.tiles0, jt = rest - si * a.tiles0;
+  const int lane = threadIdx.x & 63;
+  const bool periodic = a.periodic != 0;
+  const int hl = !periodic && a.d2 <= 64 * NC ? 0 : (R + NC - 1) / NC;
+  S s;
+  s.c = (ConstPtr<T>)a.coef;
+  s.in = (const T*)a.in;
+  s.periodic = periodic;
+  s.N = (uint32_t)a.d2;
+  s.plane = (uint32_t)(a.d1 * a.d2);
+  const int64_t N = a.d2;
+  const int64_t k0 = ((int64_t)si * (64 - 2 * hl) - hl) * NC;
+  const int64_t col = k0 + lane * NC;
+  const bool store_lane = lane >= hl && lane < 64 - hl && col < N;
+  int64_t wc = col;
+  if (periodic) {
+    wc %= N;
+    if (wc < 0) wc += N;
+  } else if (wc < 0 || wc >= N) {
+    wc = 0;
+  }
+  s.wcol = (uint32_t)wc;
+#pragma unroll
+  for (int e = 0; e < NC; ++e) s.ok[e] = periodic || (col + e >= 0 && col + e < N);
+  const bool split = NC > 1 && __builtin_amdgcn_ballot_w64(wc + NC > N) != 0;
+  const int Nj = (int)a.d1, j0 = jt * J;
+#pragma unroll
+  for (int x = 0; x < S::XR; ++x) {
+    int r = j0 - R + x;
+    s.rok[x] = true;
+    if (r < 0 || r >= Nj) {
+      s.rok[x] = periodic;
+      r = periodic ? r % Nj : 0;
+      if (r < 0) r += Nj;
+    }
+    s.roff[x] = (uint32_t)r * s.N;
+  }
+  const bool edge = !periodic && (k0 < 0 || k0 + 64 * NC > N || j0 < R || j0 + J + R > Nj);
+  if (split) s.template point<2>(o, a.d0);
+  else if (edge) s.template point<1>(o, a.d0);
+  else s.template point<0>(o, a.d0);
+  if (!store_lane) return;
+  T* out = (T*)a.out + (int64_t)o * s.plane + col;
+#pragma unroll
+  for (int p = 0; p < J; ++p) {
+    if (j0 + p >= Nj) break;
+    T* dst = out + (uint32_t)(j0 + p) * s.N;
+    if (col + NC <= N) {
+      RsPack<T, NC> v;
+#pragma unroll
+      for (int k = 0; k < NC; ++k) v.v[k] = s.acc[p][k];
+      *reinterpret_cast<RsPack<T, NC>*>(dst) = v;
+    } else {
+#pragma unroll
+      for (int k = 0; k < NC; ++k)
+        if (col + k < N) dst[k] = s.acc[p][k];
+    }
+  }
+}
+
+template <typename T, int R, bool BOX, int NC, int J>
+__global__ __launch_bounds__(256) void rows3d_kernel(KArgs a) {
+  rows3d_item<T, R, BOX, NC, J>(a, xcd_remap(blockIdx.x, gridDim.x));
+}
+
+template <typename T, int R, bool BOX, int NC, int J>
+__global__ __launch_bounds__(256) void rows3d_batch(BatchArgs b) {
+  for_each_batch_item(b, [&](const KArgs& x, int id) { rows3d_item<T, R, BOX, NC, J>(x, id); });
+}
+
+// ------------------------------------------------------------------ host
+// The shapes built, NC x J: 1 x 2, 1 x 4, 2 x 4 and 4 x 4 (FP64 orders 3 and 4: 4 x 2,
+// the wider rows' registers leave one wave per SIMD otherwise: 256^3 FP64
+// order-4 box 572 -> 504 us).
+constexpr int rows3d_j(int es, int R, int NC, bool tall) {
+  return NC == 1 ? (tall ? 4 : 2) : (NC == 4 && es == 8 && R >= 3) ? 2 : 4;
+}
+
+struct Rows3DCut {
+  int NC = 0, J = 0;
+  int64_t strips = 0, groups = 0, waves = 0;
+  double time = 0.0;  // us, estimated
+};
+
+// One shape's cut and time: issue slots of a wave (the FMAs, FP64 ones at
+// about half the FP32 rate; about three slots per halo column moved; the loads)
+// over the 2048 waves that issue at once, 4 cycles each at 2.1 GHz, and the factor
+// that boxes measured (256^3 FP32 order 3: 108 us of slots, 167 measured;
+// order 4: 228, 344; FP64 order 3: 230, 268; order 4: 483, 504).
+inline Rows3DCut rows3d_cut(const KArgs& a, int R, bool box, int es, int NC, int J) {
+  Rows3DCut c;
+  c.NC = NC;
+  c.J = J;
+  const int W = 2 * R + 1, XR = J + 2 * R;
+  const int hl = !a.periodic && a.d2 <= 64 * NC ? 0 : (R + NC - 1) / NC;
+  const int cols = (64 - 2 * hl) * NC;
+  c.strips = (a.d2 + cols - 1) / cols;
+  c.groups = (a.d1 + J - 1) / J;
+  c.waves = c.strips * c.groups * a.d0;
+  const double f = es == 8 ? 1.85 : 1.0, move = 6.0 * R * (es / 4);
+  const double slots = box ? W * (XR * (move + 8) + J * NC * W * W * f + (es == 4 ? W * W : 0))
+                           : XR * 8.0 + 2 * R * J * 8.0 + J * move + J * NC * (6 * R + 1) * f;
+  c.time = 2.5 + (es == 8 && R >= 3 ? 1.1 : 1.45) * slots * std::max(1.0, c.waves / 2048.0) * 4.0 / 2100.0;
+  return c;
+}
+
+// The best shape for a grid (alone: the shortest estimate; one of several: one
+// lane column up to 200 columns, as each shape more is a launch more), NC = 0 when
+// the kernel's 32-bit indices do not reach.
+inline Rows3DCut rows3d_best(const KArgs& a, int R, bool box, int es) {
+  Rows3DCut best;
+  if (a.d1 * a.d2 >= (int64_t(1) << 31)) return best;
+  for (int k = 0; k < 4; ++k) {
+    const int NC = k < 2 ? 1 : k == 2 ? 2 : 4;
+    if (NC > a.d2) continue;
+    if (a.share > 0 && k != (a.d2 <= 200 ? 1 : 3)) continue;
+    const Rows3DCut c = rows3d_cut(a, R, box, es, NC, rows3d_j(es, R, NC, k == 1));
+    if (c.waves >= (int64_t(1) << 31) - 4 || (best.NC && c.time >= best.time)) continue;
+    best = c;
+  }
+  return best;
+}
+
+// Whether the cut beats the plane ring: on ragged or misaligned grids always (the
+// ring stages those without overlap); else on small grids, and for boxes from
+// order 2 where the estimate is below the ring's time per point (ps) at 256^3 and
+// 512^3.
+// Larger stars and 27-point boxes are bound by memory, where the ring reads a
+// plane once: 512^3 FP32 star 212-248 us against 311-690, 256^3 25-39 against 24-46.
+template <typename T, int R, bool BOX>
+inline bool rows3d_better(const KArgs& a, const Rows3DCut& c) {
+  if (!dma3d_ok<T>(a)) return true;
+  const double pts = (double)a.d0 * (double)a.d1 * (double)a.d2;
+  if (pts * sizeof(T) <= 32e6) return true;
+  constexpr double ring_ps[2][2][5] = {{{0, 0, 5.9, 25.4, 48.3}, {0, 0, 9.7, 27.2, 82.5}},
+                                       {{0, 0, 4.2, 16.2, 34.6}, {0, 0, 7.2, 20.8, 66.6}}};
+  return BOX && R >= 2 && c.time < pts * ring_ps[pts < 3e7 ? 0 : 1][sizeof(T) / 8][R] * 1e-6;
+}
+
+// AUTO's choice between the cut and the n = 4 outer products for FP32 boxes of
+// order 3 and 4: those take 97 / 225 us however small the grid, and 14.2 / 25.7 ps a
+// point at 256^3, 11.4 / 20.9 at 320^3, 8.9 / 16.6 at 512^3 (the rows: 10.0 / 20.5 at
+// 256^3, 13.4 / 28.2 at 320^3).  Up to 16^3 the outer products stay, the choice their
+// callers know.
+inline bool rows3d_beats_mfma(const Rows3DCut& c, int R, double pts) {
+  const double ps = R == 3 ? (pts < 2e7 ? 13.5 : pts < 5e7 ? 11.0 : 8.9) : (pts < 2e7 ? 25.0 : pts < 5e7 ? 20.5 : 16.6);
+  return c.NC && pts > 4096 && c.time < std::max(R == 3 ? 97.0 : 225.0, pts * ps * 1e-6);
+}
+
+// The kernel of a cut (NC x J built above).
+template <typename T, bool BOX>
+Kernel rows3d_of(int R, int NC, int J, int64_t items);
+
+// Its args and kernel.
+template <typename T, int R, bool BOX>
+inline Kernel rows3d_kernel_for(KArgs& a, const Rows3DCut& c) {
+  a.tiles0 = (int32_t)c.groups;
+  a.tiles1 = (int32_t)c.strips;
+  return rows3d_of<T, BOX>(R, c.NC, c.J, (c.waves + 3) / 4);
+}
+
+}  // namespace stencil

@@ -1,0 +1,8 @@
+// 3D gather on register rows: F64 star stencils.
+#include "kernels_rows3d_inst.hpp"
+
+namespace stencil {
+
+template Kernel rows3d_of<double, false>(int R, int NC, int J, int64_t items);
+
+}  // namespace stencil

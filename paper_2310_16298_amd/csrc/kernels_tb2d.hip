@@ -41,16 +41,16 @@ void rs2d_batch_cut(const std::vector<const Resolved*>& grids, std::vector<int>*
   if (*columns == 0) *columns = 1;
 }
 
-// Cuts the grid (MANY: for the NC in a.tiles0 and the share of the waves in
-// a.nchunks) and returns NC.
+// Cuts the grid (MANY: for the NC in a.columns and the share of the waves in
+// a.share) and returns NC.
 template <typename T, int R, bool BOX, bool MANY>
 static int cut_rs2d(KArgs& a) {
   const KArgs in = a;
   int best = 0;
   double best_time = 0.0;
   for (int NC = 1; NC <= 4; NC *= 2) {
-    if (MANY && NC != in.tiles0) continue;
-    const int64_t waves_for = MANY ? in.nchunks : kRsWaves;
+    if (MANY && NC != in.columns) continue;
+    const int64_t waves_for = MANY ? in.share : kRsWaves;
     const RsCut c = rs_cut(in, R, BOX, (int)sizeof(T), in.steps, NC, waves_for, MANY);
     const double waves = (double)(c.strips * c.chunks);
     const double t = c.wave * std::max(1.0, waves / (double)waves_for);

@@ -18,6 +18,7 @@
 #include <cstring>
 
 #include "kernels_3d.hpp"
+#include "kernels_rows3d.hpp"
 
 namespace stencil {
 
@@ -444,7 +445,15 @@ int resolve_plan(const stencil_desc_t* desc, Resolved* rs, bool pack) {
       // outer products up to 88 (r = 3) / 128 (r = 4) taps (256^3 FP32)
       static const int kSparse3DAuto[5] = {0, 0, 0, 88, 128};
       const bool few = general && in.taps <= kSparse3DAuto[R];
-      path = f32 && box && R >= 3 && !few ? STENCIL_PATH_MFMA : STENCIL_PATH_GATHER;
+      KArgs dims{};
+      dims.d0 = d.dims[0];
+      dims.d1 = d.dims[1];
+      dims.d2 = d.dims[2];
+      dims.periodic = d.boundary == STENCIL_BC_PERIODIC;
+      const bool rows = f32 && d.shape == STENCIL_BOX && R >= 3 && d.chunk == 0 && d.block_n == 0 &&
+                        rows3d_beats_mfma(rows3d_best(dims, R, true, 4), R,
+                                          (double)dims.d0 * (double)dims.d1 * (double)dims.d2);
+      path = f32 && box && R >= 3 && !few && !rows ? STENCIL_PATH_MFMA : STENCIL_PATH_GATHER;
       // Time blocking, two steps per launch, on k extents that take
       // direct-to-LDS lines, when every knob is left open; measured on MI355X
       // (zero halo) against the one-step gather: the whole-window form on

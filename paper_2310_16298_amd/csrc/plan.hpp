@@ -83,8 +83,8 @@ Picker find_mfma3d(int dtype, int R, bool box);
 Picker find_mfma3d_b4(int R, bool box);  // FP32 n = 4 blocks: stars, 27-point box
 Picker find_split3d(int kind, int R, bool box, bool hybrid);  // hybrid: stars, lines along j and k on MFMA
 Picker find_tb2d(int dtype, int R, bool box);
-// Among many grids: reads the columns per lane and the grid's share of the
-// waves, which rs2d_batch_cut chooses, from a.tiles0 and a.nchunks.
+// Among many grids: takes the columns per lane and the share of the waves that
+// rs2d_batch_cut chooses.
 Picker find_tb2d_batch(int dtype, int R, bool box);
 void rs2d_batch_cut(const std::vector<const Resolved*>& grids, std::vector<int>* share, int* columns);
 Picker find_tb3d(int dtype, int R, bool box);  // two steps per launch

@@ -119,14 +119,12 @@ inline stencil_status_t check_device(int device) {
 
 // The resolved plan's args with the two buffers and the launch's step count
 // filled in, its kernel picked (by `pick`, else the plan's own picker) and the
-// decomposition applied.  columns / share: the cut of a 2D gather in a batch.
+// decomposition applied.  share > 0: one of several grids in a launch.
 inline Kernel plan_kernel(const Resolved& rs, const void* in, void* out, KArgs* a, int fused = 1,
                           Picker pick = nullptr, int columns = 0, int share = 0) {
   *a = rs.args;
-  if (columns > 0) {
-    a->tiles0 = columns;
-    a->nchunks = share;
-  }
+  a->columns = columns;
+  a->share = share;
   a->in = in;
   a->out = out;
   a->steps = fused;

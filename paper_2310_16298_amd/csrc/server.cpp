@@ -230,8 +230,7 @@ stencil_status_t admit(stencil_server_s* s, Request* r) {
   a.zeros = zeros;
   a.in = b0;
   a.out = b1;
-  // one of several grids in a launch: a quarter of a full launch's waves
-  if (r->rs.family == FAM_GATHER2D || r->rs.family == FAM_TB2D) a.nchunks = 512;
+  a.share = 512;  // one of several grids in a launch: a quarter of a full launch's waves
   r->kernel = r->rs.pick(a, r->rs.chunk_req);
   if (!r->kernel.launch_batch || r->kernel.items < 1) return STENCIL_EINTERNAL;
   r->args = a;
