@@ -4,6 +4,7 @@
 #include <cstring>
 #include <map>
 #include <new>
+#include <set>
 #include <tuple>
 #include <vector>
 
@@ -170,24 +171,35 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       b->groups.back().k = k;
       return b->groups.size() - 1;
     };
-    // columns per lane and shares of the waves of the 2D gathers, by class
+    struct Plain {
+      KArgs a;
+      Kernel k;
+    };
+    std::vector<Plain> plain;  // grids of one step per launch
+    // columns per lane and shares of the waves of the gathers, by class
     std::vector<int> columns(count, 0), share(count, 1);
     std::map<std::pair<Picker, int>, std::vector<int32_t>> members;
     for (int32_t i = 0; i < count; ++i) {
       const Resolved& rs = plans[i]->rs;
       if (rs.family == FAM_TB2D) members[{rs.pick_batch, rs.time_block}].push_back(i);
-      if (rs.family == FAM_GATHER2D) members[{rs.pick, 1}].push_back(i);
+      if (rs.family == FAM_GATHER2D || rs.family == FAM_GATHER3D || rs.family == FAM_TB3D)
+        members[{rs.pick, 1}].push_back(i);
     }
     for (const auto& m : members) {
       std::vector<const Resolved*> grids;
-      for (int32_t i : m.second) grids.push_back(&plans[i]->rs);
-      std::vector<int> sh;
-      int nc = 0;
-      rs2d_batch_cut(grids, &sh, &nc);
-      for (size_t k = 0; k < m.second.size(); ++k) {
-        columns[m.second[k]] = nc;
-        share[m.second[k]] = sh[k];
+      double bytes = 0.0;
+      for (int32_t i : m.second) {
+        grids.push_back(&plans[i]->rs);
+        bytes += (double)plans[i]->grid_bytes;
       }
+      // 2D: a grid's part of the class's bytes; 3D: an even part (whether small
+      // grids take a workgroup each goes by their number)
+      const bool d2 = grids[0]->info.ndim == 2;
+      for (int32_t i : m.second)
+        share[i] = std::max(1, (int)(2048.0 * (d2 ? (double)plans[i]->grid_bytes / bytes : 1.0 / (double)grids.size())));
+      if (!d2) continue;
+      const int nc = rs2d_batch_cut(grids, share.data(), m.second.data());
+      for (int32_t i : m.second) columns[i] = nc;
     }
     for (int32_t i = 0; i < count; ++i) {
       const Resolved& rs = plans[i]->rs;
@@ -228,18 +240,28 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
         }
       }
       if (placed) continue;
-      KArgs a;
-      const Kernel k = plan_kernel(rs, buf0[i], buf1[i], &a, 1, nullptr, columns[i], share[i]);
-      if (!k.launch || k.items < 1) {
+      plain.emplace_back();
+      plain.back().k = plan_kernel(rs, buf0[i], buf1[i], &plain.back().a, 1, nullptr, columns[i], share[i]);
+      if (!plain.back().k.launch || plain.back().k.items < 1) {
         delete b;
         return STENCIL_EINTERNAL;
       }
-      auto it = by_kernel.find(k.batch_id);
+    }
+    // plain grids by kernel, or by the kernel several of theirs merge into
+    std::map<const void*, std::set<const void*>> kinds;
+    for (const Plain& p : plain)
+      if (p.k.merged_id) kinds[p.k.merged_id].insert(p.k.batch_id);
+    for (Plain& p : plain) {
+      if (p.k.merged_id && kinds[p.k.merged_id].size() > 1) {
+        p.k.batch_id = p.k.merged_id;
+        p.k.launch_batch = p.k.launch_merged;
+      }
+      auto it = by_kernel.find(p.k.batch_id);
       if (it == by_kernel.end()) {
-        it = by_kernel.emplace(k.batch_id, new_group(k)).first;
+        it = by_kernel.emplace(p.k.batch_id, new_group(p.k)).first;
         b->plain.push_back(it->second);
       }
-      if (!add_grid(it->second, a, k)) {
+      if (!add_grid(it->second, p.a, p.k)) {
         delete b;
         return STENCIL_EUNSUPPORTED;
       }

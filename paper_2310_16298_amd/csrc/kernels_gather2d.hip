@@ -43,7 +43,10 @@ static Kernel pick_gather2d(KArgs& a, int32_t chunk) {
       a.tiles1 = (int32_t)c.strips;
       a.chunk = (int32_t)c.ch;
       a.nchunks = (int32_t)c.chunks;
-      return rs2d_one<T, BOX>(R, (c.strips * c.chunks + 3) / 4);
+      a.variant = 2 * R + (BOX ? 1 : 0);
+      Kernel k = rs2d_one<T, BOX>(R, (c.strips * c.chunks + 3) / 4);
+      rs2d_one_merge<T>(&k);
+      return k;
     }
   }
   // FP32 grids at most one 64-column tile wide: the 64 x 64 tiled kernel

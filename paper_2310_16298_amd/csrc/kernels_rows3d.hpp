@@ -292,6 +292,25 @@ __global__ __launch_bounds__(256) void rows3d_batch(BatchArgs b) {
   for_each_batch_item(b, [&](const KArgs& x, int id) { rows3d_item<T, R, BOX, NC, J>(x, id); });
 }
 
+// Batched, every order and shape in one kernel (NC = 1, J = 4).  A mixed batch is
+// bound by its launches: 120 FP64 grids of 64^2 .. 64^3, 10 steps, spent 150 of 178
+// launches on 3D kernels of its own each.
+template <typename T>
+__global__ __launch_bounds__(256) void rows3d_merged(BatchArgs b) {
+  for_each_batch_item(b, [&](const KArgs& x, int id) {
+    switch (x.variant) {
+      case 2: rows3d_item<T, 1, false, 1, 4>(x, id); break;
+      case 3: rows3d_item<T, 1, true, 1, 4>(x, id); break;
+      case 4: rows3d_item<T, 2, false, 1, 4>(x, id); break;
+      case 5: rows3d_item<T, 2, true, 1, 4>(x, id); break;
+      case 6: rows3d_item<T, 3, false, 1, 4>(x, id); break;
+      case 7: rows3d_item<T, 3, true, 1, 4>(x, id); break;
+      case 8: rows3d_item<T, 4, false, 1, 4>(x, id); break;
+      case 9: rows3d_item<T, 4, true, 1, 4>(x, id); break;
+    }
+  });
+}
+
 // ------------------------------------------------------------------ host
 // The shapes built, NC x J: 1 x 2, 1 x 4, 2 x 4 and 4 x 4 (FP64 orders 3 and 4: 4 x 2,
 // the wider rows' registers leave one wave per SIMD otherwise: 256^3 FP64
@@ -374,13 +393,20 @@ inline bool rows3d_beats_mfma(const Rows3DCut& c, int R, double pts) {
 // The kernel of a cut (NC x J built above).
 template <typename T, bool BOX>
 Kernel rows3d_of(int R, int NC, int J, int64_t items);
+template <typename T>
+void rows3d_merge(Kernel* k);
 
 // Its args and kernel.
 template <typename T, int R, bool BOX>
 inline Kernel rows3d_kernel_for(KArgs& a, const Rows3DCut& c) {
   a.tiles0 = (int32_t)c.groups;
   a.tiles1 = (int32_t)c.strips;
-  return rows3d_of<T, BOX>(R, c.NC, c.J, (c.waves + 3) / 4);
+  Kernel k = rows3d_of<T, BOX>(R, c.NC, c.J, (c.waves + 3) / 4);
+  if (c.NC == 1 && c.J == 4) {
+    a.variant = 2 * R + (BOX ? 1 : 0);
+    rows3d_merge<T>(&k);
+  }
+  return k;
 }
 
 }  // namespace stencil

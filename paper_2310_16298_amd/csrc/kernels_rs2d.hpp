@@ -162,6 +162,7 @@ struct RsWave {
   uint32_t col;        // the lane's first column (stored ones: inside the grid) ...
   uint32_t wcol;       // ... wrapped / clamped into the row
   bool periodic, store_lane;
+  int turn;            // 0 or 1: the workgroup's place on its CU
   bool ok[NC];         // column col + e lies in the grid
 
   __device__ __forceinline__ void hold(ConstPtr<T> c) {
@@ -319,6 +320,11 @@ struct RsWave {
   __device__ __forceinline__ void rows(int n, int first, int ch, T (*nx)[NC]) {
 #pragma unroll 1
     for (int i = 0; i < n; i += U) {
+      // The two waves of a SIMD take turns at being served first, 16 rows each:
+      // always the older first, it ends early and the other walks on alone
+      // (8192^2 FP32 boxes r = 1, 3, 4 +5 / +2 / +3 %, 2048^2 order-2 box +4 %).
+      if ((i >> 4 ^ turn) & 1) __builtin_amdgcn_s_setprio(1);
+      else __builtin_amdgcn_s_setprio(0);
 #pragma unroll
       for (int u = 0; u < U; ++u) one<L, MODE>(i + u >= first && i + u < first + ch, nx[u]);
     }
@@ -356,6 +362,7 @@ __device__ __forceinline__ void rs2d_item(const KArgs& a, int item) {
   const int hl = rs2d_halo_lanes(a, R, NC);  // stale lanes per side
   RsWave<T, R, BOX, TS, NC> w;
   w.hold((ConstPtr<T>)a.coef);
+  w.turn = (int)(blockIdx.x >> 8) & 1;  // one workgroup per CU before the next ones
   w.in = (const T*)a.in;
   w.out = (T*)a.out;
   w.M = (uint32_t)a.d0;
@@ -410,6 +417,23 @@ __global__ __launch_bounds__(256) void rs2d_batch(BatchArgs b) {
   for_each_batch_item(b, [&](const KArgs& x, int id) { rs2d_item<T, R, BOX, TS, NC>(x, id); });
 }
 
+// Batched single steps, every order and shape in one kernel (NC = 2).
+template <typename T>
+__global__ __launch_bounds__(256) void rs2d_one_merged(BatchArgs b) {
+  for_each_batch_item(b, [&](const KArgs& x, int id) {
+    switch (x.variant) {
+      case 2: rs2d_item<T, 1, false, 1, 2>(x, id); break;
+      case 3: rs2d_item<T, 1, true, 1, 2>(x, id); break;
+      case 4: rs2d_item<T, 2, false, 1, 2>(x, id); break;
+      case 5: rs2d_item<T, 2, true, 1, 2>(x, id); break;
+      case 6: rs2d_item<T, 3, false, 1, 2>(x, id); break;
+      case 7: rs2d_item<T, 3, true, 1, 2>(x, id); break;
+      case 8: rs2d_item<T, 4, false, 1, 2>(x, id); break;
+      case 9: rs2d_item<T, 4, true, 1, 2>(x, id); break;
+    }
+  });
+}
+
 // Work decomposition of the register-streaming kernel: strips of 64 NC
 // columns, chunks of rows.  A launch runs two waves per SIMD (kRsWaves = 2048 on
 // 256 CUs), each with an issue port of its own, so a grid alone is cut into
@@ -459,5 +483,7 @@ Kernel rs2d_of(int R, int NC, int64_t items);
 // The same walk with one step (NC = 2).
 template <typename T, bool BOX>
 Kernel rs2d_one(int R, int64_t items);
+template <typename T>
+void rs2d_one_merge(Kernel* k);
 
 }  // namespace stencil

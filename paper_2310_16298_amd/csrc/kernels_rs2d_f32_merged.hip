@@ -1,0 +1,11 @@
+// Register-streaming 2D gather, one step: the batched kernel of all F32 stencils.
+#include "kernels_rs2d.hpp"
+
+namespace stencil {
+
+template <>
+void rs2d_one_merge<float>(Kernel* k) {
+  merge_into<rs2d_one_merged<float>>(k);
+}
+
+}  // namespace stencil

@@ -11,15 +11,9 @@ namespace stencil {
 
 // The grids of one batch class (same type, order, shape and step count) share
 // one kernel, so one NC: the one with the shortest class time, its work over
-// the full chip or its longest wave.  A grid's share of the waves goes by its
-// bytes.
-void rs2d_batch_cut(const std::vector<const Resolved*>& grids, std::vector<int>* share, int* columns) {
-  double all = 0.0;
-  for (const Resolved* g : grids) all += (double)g->args.d0 * (double)g->args.d1;
-  share->clear();
-  for (const Resolved* g : grids)
-    share->push_back(std::max(1, (int)(kRsWaves * ((double)g->args.d0 * (double)g->args.d1 / all))));
-  *columns = 0;
+// the full chip or its longest wave.  index[k]: grid k's place in share.
+int rs2d_batch_cut(const std::vector<const Resolved*>& grids, const int* share, const int32_t* index) {
+  int columns = 0;
   double best = 0.0;
   for (int NC = 1; NC <= 4; NC *= 2) {
     double work = 0.0, longest = 0.0;
@@ -27,18 +21,18 @@ void rs2d_batch_cut(const std::vector<const Resolved*>& grids, std::vector<int>*
     for (size_t k = 0; k < grids.size() && ok; ++k) {
       const Resolved& g = *grids[k];
       const RsCut c = rs_cut(g.args, g.info.radius, g.info.shape != STENCIL_STAR, g.info.dtype == STENCIL_F64 ? 8 : 4,
-                             g.time_block, NC, (*share)[k], true);
+                             g.time_block, NC, share[index[k]], true);
       ok = rs_columns_ok(g.args, NC, c);
       const double wave = c.wave + 1500.0;  // finding the grid, its weights, the first rows
       work += wave * (double)(c.strips * c.chunks);
       longest = std::max(longest, wave);
     }
     const double t = std::max(work / kRsWaves, longest);
-    if (!ok || (*columns && t >= best)) continue;
-    *columns = NC;
+    if (!ok || (columns && t >= best)) continue;
+    columns = NC;
     best = t;
   }
-  if (*columns == 0) *columns = 1;
+  return columns ? columns : 1;
 }
 
 // Cuts the grid (MANY: for the NC in a.columns and the share of the waves in

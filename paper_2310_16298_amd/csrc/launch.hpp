@@ -25,6 +25,11 @@ struct Kernel {
   const void* batch_id = nullptr;      // the batched __global__ function: grouping and occupancy queries
   int64_t items = 0;                   // work items (workgroup tiles) of the grid
   int threads = 256;                   // threads per workgroup (both entry points)
+  // A batched kernel that serves other stencils as well (args.variant tells
+  // them apart): launches that would otherwise go to several kernels of the
+  // same merged_id are made as one.
+  BatchLaunch launch_merged = nullptr;
+  const void* merged_id = nullptr;
 };
 
 // chunk: requested rows (2D) / planes (3D) per work item, 0 = library choice.
@@ -65,6 +70,13 @@ inline Kernel kernel_of(int64_t items) {
   k.batch_id = reinterpret_cast<const void*>(KB);
   k.items = items;
   return k;
+}
+
+// The batched kernel KM for several stencils, of k's workgroup size.
+template <auto KM, int NT = 256>
+inline void merge_into(Kernel* k) {
+  k->launch_merged = launch_batched<KM, NT>;
+  k->merged_id = reinterpret_cast<const void*>(KM);
 }
 
 // A kernel that is only launched for one grid.

@@ -86,7 +86,7 @@ Picker find_tb2d(int dtype, int R, bool box);
 // Among many grids: takes the columns per lane and the share of the waves that
 // rs2d_batch_cut chooses.
 Picker find_tb2d_batch(int dtype, int R, bool box);
-void rs2d_batch_cut(const std::vector<const Resolved*>& grids, std::vector<int>* share, int* columns);
+int rs2d_batch_cut(const std::vector<const Resolved*>& grids, const int* share, const int32_t* index);
 Picker find_tb3d(int dtype, int R, bool box);  // two steps per launch
 Picker find_tb3d_batch(int dtype, int R, bool box);  // among many grids: the streaming form or none
 Picker find_tbm2d(int R);  // FP32 2D box outer products, two steps per launch

@@ -18,6 +18,7 @@
 #include <deque>
 #include <map>
 #include <new>
+#include <set>
 #include <vector>
 
 #include "runtime.hpp"
@@ -244,12 +245,22 @@ stencil_status_t rebuild_tables(stencil_server_s* s) {
   s->groups.clear();
   std::map<const void*, size_t> by_kernel;
   std::vector<std::vector<Request*>> members;
+  // requests by kernel, or by the kernel several of theirs merge into
+  std::map<const void*, std::set<const void*>> kinds;
+  for (Request* r : s->active)
+    if (r->kernel.merged_id) kinds[r->kernel.merged_id].insert(r->kernel.batch_id);
   for (Request* r : s->active) {
-    auto it = by_kernel.find(r->kernel.batch_id);
+    const bool merged = r->kernel.merged_id && kinds[r->kernel.merged_id].size() > 1;
+    const void* id = merged ? r->kernel.merged_id : r->kernel.batch_id;
+    auto it = by_kernel.find(id);
     if (it == by_kernel.end()) {
-      it = by_kernel.emplace(r->kernel.batch_id, s->groups.size()).first;
+      it = by_kernel.emplace(id, s->groups.size()).first;
       s->groups.emplace_back();
       s->groups.back().k = r->kernel;
+      if (merged) {
+        s->groups.back().k.batch_id = id;
+        s->groups.back().k.launch_batch = r->kernel.launch_merged;
+      }
       members.emplace_back();
     }
     members[it->second].push_back(r);
