@@ -16,6 +16,7 @@
 // that do not allow 16-byte lines) each plane is staged synchronously.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -67,6 +68,20 @@ inline int64_t balanced_items3d(KArgs& a, const void* kernel, int R, int32_t chu
     a.nchunks = (int32_t)((a.d0 + chunk - 1) / chunk);
     return chunk3d_items(a);
   };
+  // A grid alone with fewer items than CUs: shorter chunks, down to one plane,
+  // until there is one per CU -- its time is that of one item, chunk + 2r planes
+  // (MI355X, us a step: 64^3 split star r = 4 35 -> 14, split box r = 4 149 -> 54,
+  // outer products star r = 2 12.6 -> 6.2, box r = 4 223 -> 88; 128^3 37 -> 20, 148 -> 74,
+  // 13.5 -> 9.7, 225 -> 116).  Among many grids the shorter chunks' warm-up planes
+  // would cost instead.
+  if (a.share == 0 && items < res.cus) {
+    const int64_t chunk = std::max<int64_t>(1, (a.d0 * tiles + res.cus - 1) / res.cus);
+    if (chunk < a.chunk) {
+      a.chunk = (int32_t)chunk;
+      a.nchunks = (int32_t)((a.d0 + chunk - 1) / chunk);
+    }
+    return chunk3d_items(a);
+  }
   const int64_t slots = (int64_t)per_cu * res.cus;
   if (per_cu <= 3 && items > slots) return recut(slots / tiles);
   // Even fill: the plan rounds its chunk count up from an item target, which
