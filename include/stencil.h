@@ -96,7 +96,7 @@ typedef enum {
                                    12910 + 1530 L (2r+4)/12 for L lines), GATHER otherwise; 2D
                                    grids of at most 64 columns (stars, the F64 9-point box), or
                                    of at most 68 and not a multiple of 4, take MFMA, and so do
-                                   GENERAL ones of any other extent not a multiple of 4;
+                                   F32 GENERAL ones of any other extent not a multiple of 4;
                                    stencil_plan_info reports the choice */
   STENCIL_PATH_GATHER = 1,      /* gather-form vector kernel, Eq. (1) */
   STENCIL_PATH_MFMA = 2,        /* outer-product form on MFMA in the grid dtype (FP32 or FP64) */
@@ -157,7 +157,7 @@ typedef struct {
                            lines, block_n, chunk, reg_rows and tile_width all 0, takes the
                            time-blocked gather with T measured fastest on MI355X (r = 1..4,
                            F32 stars 8 / 4 / 4 / 3, boxes 8 / 4 / 4 / 2; F64 stars 8 / 4 / 2 /
-                           2, boxes 8 / 4 / - / -), and AUTO on 3D grids whose last extent is a
+                           2, boxes 8 / 4 / 2 (more than 96 columns) / -), and AUTO on 3D grids whose last extent is a
                            multiple of 4 takes T = 2 for r = 1 STAR / BOX grids of at most 64^3
                            points (F32 stars: 128^3) and for planes of many 32 x 64 (j, k) tiles:
                            at least 32 (r = 1 STARs), 48 (F32 r = 2 STAR), 64 (F64 r = 1 BOX) or

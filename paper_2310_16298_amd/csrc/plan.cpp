@@ -501,26 +501,32 @@ int resolve_plan(const stencil_desc_t* desc, Resolved* rs, bool pack) {
       // stars 14-15 us against 5.5-6.9, boxes r = 3, 4 18-19 against 8.8-11.8, FP64
       // boxes 17-34 against 6-18; 75^2 17-22 against 3.6-7.5).  Up to 68 columns
       // such grids keep the outer products, the choice their callers know.
-      const bool ragged = !dma_cols && d.dims[1] > 68 && !general;
+      // FP64 GENERAL ones take the all-tap gather, one step per launch (5413 x 2017,
+      // order 4: 191 us a step as a line cover, 55); FP32 ones keep the cover.
+      const bool ragged = !dma_cols && d.dims[1] > 68 && !(general && f32) && d.lines == STENCIL_LINES_AUTO && d.block_n == 0 &&
+                          d.reg_rows == 0 && d.tile_width == 0;
       path = (dma_cols && !heavy && !narrow) || ragged ? STENCIL_PATH_GATHER : STENCIL_PATH_MFMA;
       // Time blocking: the time-blocked gather with the step count measured
       // fastest on MI355X (512^2, 2048^2 and 8192^2, periodic) beats every
-      // one-step plan.  On
-      // narrow grids too (10 steps, alone: 32^2, 48^2, 32 x 128 and 64^2 take
+      // one-step plan.  On narrow grids too (10 steps, alone: 32^2, 48^2, 32 x 128 and 64^2 take
       // 24-60 us against 50-108 us for the best one-step plan; batches of 64^2
       // grids run 1.6-2.1x faster), except the FP32 box of order 4, which
-      // keeps the outer products up to 64 columns (69 vs 73-76 us).  FP32: 8 / 4 / 4 / 3 steps per launch for stars of order 1..4,
+      // keeps the outer products up to 64 columns (69 vs 73-76 us).
+      // FP32: 8 / 4 / 4 / 3 steps per launch for stars of order 1..4,
       // 8 / 4 / 4 / 2 for boxes (ahead of the outer products by 2-4 % at
       // order 3 and 7-10 % at order 4 on 8192^2, by 1.1-1.4x on 2048^2).
-      // FP64: stars 8 / 4 / 2 / 2, boxes 8 / 4 and none from order 3 (their
-      // 49 / 81 weights take 98 / 162 vector registers there).  Only when
-      // every kernel knob is left to the library.
+      // FP64: stars 8 / 4 / 2 / 2, boxes 8 / 4 / 2 and none at order 4 (bound by
+      // its 81 FMAs a point).  Only when every kernel knob is left to the library.
       static const int kAutoTimeBlock[2][2][5] = {{{0, 8, 4, 4, 3}, {0, 8, 4, 4, 2}},   // F32 star, box
                                                   {{0, 8, 4, 2, 2}, {0, 8, 4, 0, 0}}};  // F64 star, box
       const bool tb_cols = d.dims[1] > 64 || !(f32 && box && R == 4);
       if (!general && (dma_cols || ragged) && tb_cols && d.time_block == 0 && d.lines == STENCIL_LINES_AUTO &&
           d.block_n == 0 && d.chunk == 0 && d.reg_rows == 0 && d.tile_width == 0) {
-        const int t = kAutoTimeBlock[f32 ? 0 : 1][box ? 1 : 0][R];
+        int t = kAutoTimeBlock[f32 ? 0 : 1][box ? 1 : 0][R];
+        // the FP64 order-3 box: two steps with its weights in registers take 161 us
+        // a step at 8192^2 against 223 alone, 4.5 against 6.3 at 512^2; up to 96
+        // columns it keeps one step, the choice its callers know
+        if (!f32 && box && R == 3 && d.dims[1] > 96) t = 2;
         if (t > 1) {
           path = STENCIL_PATH_GATHER;
           tb_auto = t;
