@@ -174,6 +174,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
     struct Plain {
       KArgs a;
       Kernel k;
+      double flops = 0.0;  // per point
     };
     std::vector<Plain> plain;  // grids of one step per launch
     // columns per lane and shares of the waves of the gathers, by class
@@ -241,12 +242,15 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       }
       if (placed) continue;
       plain.emplace_back();
+      plain.back().flops = rs.info.executed_flops_per_point;
       plain.back().k = plan_kernel(rs, buf0[i], buf1[i], &plain.back().a, 1, nullptr, columns[i], share[i]);
       if (!plain.back().k.launch || plain.back().k.items < 1) {
         delete b;
         return STENCIL_EINTERNAL;
       }
     }
+    // the grids of the costliest items first: the last items to end are short
+    std::stable_sort(plain.begin(), plain.end(), [](const Plain& x, const Plain& y) { return x.flops > y.flops; });
     // plain grids by kernel, or by the kernel several of theirs merge into
     std::map<const void*, std::set<const void*>> kinds;
     for (const Plain& p : plain)

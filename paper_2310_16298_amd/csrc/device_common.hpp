@@ -225,16 +225,20 @@ __device__ __forceinline__ S uniform_load(const S* p) {
 
 // Batched launch: a persistent loop over work items blockIdx.x,
 // blockIdx.x + gridDim.x, ... of all grids in the table (every workgroup ends
-// after the last item); each item finds its grid by binary search over
-// `first` and runs item(args, id) with the grid's args in scalar registers.
+// after the last item); each item finds its grid over `first`, 64 entries at a
+// time (a load per round, where a binary search waits for one per halving: six
+// of them were half of a small item's time), and runs item(args, id) with the
+// grid's args in scalar registers.
 template <class F>
 __device__ __forceinline__ void for_each_batch_item(const BatchArgs& b, F item) {
   for (int it = blockIdx.x; it < b.total; it += gridDim.x) {
-    int lo = 0, hi = b.ngrids - 1;  // last grid with first <= it
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (__builtin_amdgcn_readfirstlane(b.table[mid].first) <= it) lo = mid;
-      else hi = mid - 1;
+    int lo = 0, n = b.ngrids;  // the last grid with first <= it is in lo .. lo + n - 1
+    while (n > 1) {
+      const int step = (n + 63) >> 6, at = (int)(threadIdx.x & 63) * step;
+      const bool le = at < n && b.table[lo + (at < n ? at : 0)].first <= it;  // lane 0: always
+      const int skip = (__builtin_popcountll(__builtin_amdgcn_ballot_w64(le)) - 1) * step;
+      lo += skip;
+      n = n - skip < step ? n - skip : step;
     }
     const BatchGrid e = uniform_load(&b.table[lo]);
     if (b.launch >= e.limit) continue;  // this grid has done its steps
