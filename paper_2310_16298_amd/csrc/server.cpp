@@ -265,6 +265,11 @@ stencil_status_t rebuild_tables(stencil_server_s* s) {
     }
     members[it->second].push_back(r);
   }
+  // the grids of the costliest items first: the last items to end are short
+  for (std::vector<Request*>& m : members)
+    std::stable_sort(m.begin(), m.end(), [](const Request* x, const Request* y) {
+      return x->rs.info.executed_flops_per_point > y->rs.info.executed_flops_per_point;
+    });
   const size_t n = s->active.size();
   if (n > s->table_cap) {
     // grow the table buffers (after all work that read them)
