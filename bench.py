@@ -53,7 +53,8 @@ COEF_SEED0 = 2100
 # in profiles/traffic.json is used only while these files are unchanged.
 KERNEL_SOURCES_2D = ["device_common.hpp", "stream2d.hpp", "dma2d.hpp", "kernels_2d.hpp", "kernels_split2d.hpp",
                      "mfma_traits.hpp", "kernels_mfma2d.hip", "kernels_split2d.hip", "kernels_gather2d.hip",
-                     "kernels_tb2d.hpp", "kernels_tb2d.hip", "kernels_tb2d_box.hip", "kernels_tb2d_star.hip"]
+                     "kernels_tb2d.hpp", "kernels_tb2d.hip", "kernels_tb2d_tiles.hip", "kernels_rs2d.hpp",
+                     "kernels_rs2d_inst.hpp", "kernels_rs2d_f32_box.hip", "kernels_rs2d_f32_star.hip"]
 
 
 def kernel_source_hash() -> str:
