@@ -302,7 +302,7 @@ __device__ __forceinline__ void gather3d_item(const KArgs& a, int item) {
               for (int ap = 0; ap < W; ++ap)
 #pragma unroll
                 for (int cc = 0; cc < W; ++cc) {
-                  const T w = c[(ap * W + bb) * W + cc];
+                  const T w = vector_weight<T>(c[(ap * W + bb) * W + cc]);
 #pragma unroll
                   for (int e = 0; e < 4; ++e) ring[(2 * R - ap + PH) % W][p][e] += w * v[4 - R + e + cc];
                 }
@@ -325,7 +325,7 @@ __device__ __forceinline__ void gather3d_item(const KArgs& a, int item) {
             for (int p = 0; p < 2; ++p) {
               const int bb = x - p;
               if (bb < 0 || bb > 2 * R) continue;
-              const T w = c[(R * W + bb) * W + R];
+              const T w = vector_weight<T>(c[(R * W + bb) * W + R]);
 #pragma unroll
               for (int e = 0; e < 4; ++e) ring[(R + PH) % W][p][e] += w * v[e];
             }
@@ -338,14 +338,14 @@ __device__ __forceinline__ void gather3d_item(const KArgs& a, int item) {
 #pragma unroll
             for (int cc = 0; cc < W; ++cc) {
               if (cc == R) continue;
-              const T w = c[(R * W + R) * W + cc];
+              const T w = vector_weight<T>(c[(R * W + R) * W + cc]);
 #pragma unroll
               for (int e = 0; e < 4; ++e) ring[(R + PH) % W][p][e] += w * v[4 - R + e + cc];
             }
 #pragma unroll
             for (int ap = 0; ap < W; ++ap) {
               if (ap == R) continue;
-              const T w = c[(ap * W + R) * W + R];
+              const T w = vector_weight<T>(c[(ap * W + R) * W + R]);
 #pragma unroll
               for (int e = 0; e < 4; ++e) ring[(2 * R - ap + PH) % W][p][e] += w * v[4 + e];
             }

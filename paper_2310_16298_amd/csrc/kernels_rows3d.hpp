@@ -100,8 +100,7 @@ struct Rows3D {
     T w[W * W];
 #pragma unroll
     for (int i = 0; i < W * W; ++i) {
-      w[i] = c[a * W * W + i];
-      if (sizeof(T) == 4) asm("" : "+v"(w[i]));  // a scalar operand would halve the FP32 issue rate
+      w[i] = vector_weight<T>(c[a * W * W + i]);
     }
 #pragma unroll
     for (int x = 0; x < XR; ++x) {
@@ -296,7 +295,7 @@ __global__ __launch_bounds__(256) void rows3d_batch(BatchArgs b) {
 // bound by its launches: 120 FP64 grids of 64^2 .. 64^3, 10 steps, spent 150 of 178
 // launches on 3D kernels of its own each.
 template <typename T>
-__global__ __launch_bounds__(256) void rows3d_merged(BatchArgs b) {
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void rows3d_merged(BatchArgs b) {
   for_each_batch_item(b, [&](const KArgs& x, int id) {
     switch (x.variant) {
       case 2: rows3d_item<T, 1, false, 1, 4>(x, id); break;
@@ -375,8 +374,8 @@ inline bool rows3d_better(const KArgs& a, const Rows3DCut& c) {
   if (!dma3d_ok<T>(a)) return true;
   const double pts = (double)a.d0 * (double)a.d1 * (double)a.d2;
   if (pts * sizeof(T) <= 32e6) return true;
-  constexpr double ring_ps[2][2][5] = {{{0, 0, 5.9, 25.4, 48.3}, {0, 0, 9.7, 27.2, 82.5}},
-                                       {{0, 0, 4.2, 16.2, 34.6}, {0, 0, 7.2, 20.8, 66.6}}};
+  constexpr double ring_ps[2][2][5] = {{{0, 0, 4.9, 25.4, 48.3}, {0, 0, 9.7, 27.2, 82.5}},
+                                       {{0, 0, 3.6, 16.2, 34.6}, {0, 0, 7.2, 20.8, 66.6}}};
   return BOX && R >= 2 && c.time < pts * ring_ps[pts < 3e7 ? 0 : 1][sizeof(T) / 8][R] * 1e-6;
 }
 

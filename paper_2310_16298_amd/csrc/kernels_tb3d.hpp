@@ -407,7 +407,7 @@ __device__ __forceinline__ void tb3d_stream_item(const KArgs& a, int item) {
           for (int ap = 0; ap < W; ++ap)
 #pragma unroll
             for (int cc = 0; cc < W; ++cc) {
-              const T wgt = c[(ap * W + bb) * W + cc];
+              const T wgt = vector_weight<T>(c[(ap * W + bb) * W + cc]);
 #pragma unroll
               for (int e = 0; e < 4; ++e) ring[2 * R - ap][p][e] += wgt * v[4 - R + e + cc];
             }
@@ -423,7 +423,7 @@ __device__ __forceinline__ void tb3d_stream_item(const KArgs& a, int item) {
         for (int p = 0; p < 2; ++p) {
           const int bb = x - p;
           if (bb < 0 || bb > 2 * R) continue;
-          const T wgt = c[(R * W + bb) * W + R];
+          const T wgt = vector_weight<T>(c[(R * W + bb) * W + R]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) ring[R][p][e] += wgt * v[4 + e];
         }
@@ -436,14 +436,14 @@ __device__ __forceinline__ void tb3d_stream_item(const KArgs& a, int item) {
 #pragma unroll
         for (int cc = 0; cc < W; ++cc) {
           if (cc == R) continue;
-          const T wgt = c[(R * W + R) * W + cc];
+          const T wgt = vector_weight<T>(c[(R * W + R) * W + cc]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) ring[R][p][e] += wgt * v[4 - R + e + cc];
         }
 #pragma unroll
         for (int ap = 0; ap < W; ++ap) {
           if (ap == R) continue;
-          const T wgt = c[(ap * W + R) * W + R];
+          const T wgt = vector_weight<T>(c[(ap * W + R) * W + R]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) ring[2 * R - ap][p][e] += wgt * v[4 + e];
         }
