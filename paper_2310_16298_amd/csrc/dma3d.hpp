@@ -21,9 +21,9 @@ namespace stencil {
 // scalar / vector weights: plane ring 512^3 order-2 box 560 / 481, 384^3 266 / 221,
 // 256^3 order-3 star 37.5 / 32.6; two-step stream 512^3 27-point box 213 / 182, 384^3
 // 96 / 82, order-2 star 171 / 164).  FP64 issues one wave at a time either way.
-template <typename T>
+template <typename T, bool VW = true>
 __device__ __forceinline__ T vector_weight(T w) {
-  if constexpr (sizeof(T) == 4) asm("" : "+v"(w));
+  if constexpr (sizeof(T) == 4 && VW) asm("" : "+v"(w));
   return w;
 }
 

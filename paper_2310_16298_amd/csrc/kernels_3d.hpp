@@ -247,7 +247,11 @@ struct PlaneWalk {
 // scattered (coefficient plane a reaches z = 2r - a); afterwards ring[0] is
 // complete and the ring shifts down by one.
 // ---------------------------------------------------------------------------
-template <typename T, int R, bool BOX, bool DMA>
+// VW: weights in vector registers.  Not for boxes of order 4, whose 81 take the
+// kernel from 171 to 280 registers, one wave per SIMD (256 32^3 FP32 grids 443 -> 525 us
+// a step), nor for batched stars of order 4 (124 -> 140 registers, three waves instead of
+// four: 16 128^3 grids 78 -> 87; alone at 512^3 247 -> 241).
+template <typename T, int R, bool BOX, bool DMA, bool VW>
 __device__ __forceinline__ void gather3d_item(const KArgs& a, int item) {
   constexpr int W = 2 * R + 1, VEC = 16 / (int)sizeof(T), NV = 12 / VEC;
   typedef typename Vec16<T>::type V;
@@ -302,7 +306,7 @@ __device__ __forceinline__ void gather3d_item(const KArgs& a, int item) {
               for (int ap = 0; ap < W; ++ap)
 #pragma unroll
                 for (int cc = 0; cc < W; ++cc) {
-                  const T w = vector_weight<T>(c[(ap * W + bb) * W + cc]);
+                  const T w = vector_weight<T, VW>(c[(ap * W + bb) * W + cc]);
 #pragma unroll
                   for (int e = 0; e < 4; ++e) ring[(2 * R - ap + PH) % W][p][e] += w * v[4 - R + e + cc];
                 }
@@ -325,7 +329,7 @@ __device__ __forceinline__ void gather3d_item(const KArgs& a, int item) {
             for (int p = 0; p < 2; ++p) {
               const int bb = x - p;
               if (bb < 0 || bb > 2 * R) continue;
-              const T w = vector_weight<T>(c[(R * W + bb) * W + R]);
+              const T w = vector_weight<T, VW>(c[(R * W + bb) * W + R]);
 #pragma unroll
               for (int e = 0; e < 4; ++e) ring[(R + PH) % W][p][e] += w * v[e];
             }
@@ -338,14 +342,14 @@ __device__ __forceinline__ void gather3d_item(const KArgs& a, int item) {
 #pragma unroll
             for (int cc = 0; cc < W; ++cc) {
               if (cc == R) continue;
-              const T w = vector_weight<T>(c[(R * W + R) * W + cc]);
+              const T w = vector_weight<T, VW>(c[(R * W + R) * W + cc]);
 #pragma unroll
               for (int e = 0; e < 4; ++e) ring[(R + PH) % W][p][e] += w * v[4 - R + e + cc];
             }
 #pragma unroll
             for (int ap = 0; ap < W; ++ap) {
               if (ap == R) continue;
-              const T w = vector_weight<T>(c[(ap * W + R) * W + R]);
+              const T w = vector_weight<T, VW>(c[(ap * W + R) * W + R]);
 #pragma unroll
               for (int e = 0; e < 4; ++e) ring[(2 * R - ap + PH) % W][p][e] += w * v[4 + e];
             }
@@ -405,12 +409,12 @@ __device__ __forceinline__ void gather3d_item(const KArgs& a, int item) {
 
 template <typename T, int R, bool BOX, bool DMA>
 __global__ __launch_bounds__(kThreads) void gather3d_kernel(KArgs a) {
-  gather3d_item<T, R, BOX, DMA>(a, xcd_remap(blockIdx.x, gridDim.x));
+  gather3d_item<T, R, BOX, DMA, (R < 4 || !BOX)>(a, xcd_remap(blockIdx.x, gridDim.x));
 }
 
 template <typename T, int R, bool BOX, bool DMA>
 __global__ __launch_bounds__(kThreads) void gather3d_batch(BatchArgs b) {
-  for_each_batch_item(b, [&](const KArgs& x, int id) { gather3d_item<T, R, BOX, DMA>(x, id); });
+  for_each_batch_item(b, [&](const KArgs& x, int id) { gather3d_item<T, R, BOX, DMA, (R < 4)>(x, id); });
 }
 
 // ---------------------------------------------------------------------------

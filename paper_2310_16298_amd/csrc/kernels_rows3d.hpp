@@ -339,28 +339,61 @@ inline Rows3DCut rows3d_cut(const KArgs& a, int R, bool box, int es, int NC, int
   c.strips = (a.d2 + cols - 1) / cols;
   c.groups = (a.d1 + J - 1) / J;
   c.waves = c.strips * c.groups * a.d0;
+  const double grids = a.share > 0 ? 2048.0 / a.share : 1.0;  // like this one in the launch
   const double f = es == 8 ? 1.85 : 1.0, move = 6.0 * R * (es / 4);
   const double slots = box ? W * (XR * (move + 8) + J * NC * W * W * f + (es == 4 ? W * W : 0))
                            : XR * 8.0 + 2 * R * J * 8.0 + J * move + J * NC * (6 * R + 1) * f;
-  c.time = 2.5 + (es == 8 && R >= 3 ? 1.1 : 1.45) * slots * std::max(1.0, c.waves / 2048.0) * 4.0 / 2100.0;
+  c.time = 2.5 + (es == 8 && R >= 3 ? 1.1 : 1.45) * slots * std::max(1.0, c.waves * grids / 2048.0) * 4.0 / 2100.0;
   return c;
 }
 
-// The best shape for a grid (alone: the shortest estimate; one of several: one
-// lane column up to 200 columns, as each shape more is a launch more), NC = 0 when
-// the kernel's 32-bit indices do not reach.
+// The best shape for a grid, NC = 0 when the kernel's 32-bit indices do not reach.
+// Alone, and for boxes from order 3 among so many that the chip runs several
+// rounds of their waves: the shortest estimate (four 128^3 grids, one column per
+// lane or the ring / this, us a step: FP32 order-3 and -4 boxes 162 / 113, 315 / 224, FP64
+// 262 / 144, 433 / 273).  Else one of several: one lane column up to 200 columns, as
+// each shape more is a launch more.
 inline Rows3DCut rows3d_best(const KArgs& a, int R, bool box, int es) {
   Rows3DCut best;
   if (a.d1 * a.d2 >= (int64_t(1) << 31)) return best;
+  const bool full = a.share > 0 && box && R >= 3 && rows3d_cut(a, R, box, es, 1, 4).waves >= 8 * a.share;
   for (int k = 0; k < 4; ++k) {
     const int NC = k < 2 ? 1 : k == 2 ? 2 : 4;
     if (NC > a.d2) continue;
-    if (a.share > 0 && k != (a.d2 <= 200 ? 1 : 3)) continue;
+    if (a.share > 0 && (full ? k == 0 : k != (a.d2 <= 200 ? 1 : 3))) continue;
     const Rows3DCut c = rows3d_cut(a, R, box, es, NC, rows3d_j(es, R, NC, k == 1));
     if (c.waves >= (int64_t(1) << 31) - 4 || (best.NC && c.time >= best.time)) continue;
     best = c;
   }
   return best;
+}
+
+// One of many aligned grids: the rows end early (a chip's waves of them in 5-25 us),
+// the ring's few deep items late (8-400 us, ring_us) but at less cost a point, so
+// the rows serve few or small grids and the ring many.  Estimates in us from
+// batches of 4 .. 1024 grids of 24^3 .. 96^3: rows_ns a wave of one column and
+// four rows (boxes from order 3: the cut's estimate); ring_ps a point of the 32 x 64
+// tiles.  Ring / rows, us a step: FP32 order-3 star 32^3 x 16 24.9 / 8.9, x 64 26.4 /
+// 19.9, x 256 40 / 77, x 1024 117 / 268, 64^3 x 16 29 / 20, x 64 41 / 66; order-3 box
+// 48^3 x 64 224 / 156, 32^3 x 256 265 / 279; FP64 order-4 star 64^3 x 64 61 / 140.
+inline bool rows3d_better_many(const KArgs& a, const Rows3DCut& c, int R, bool box, int es) {
+  constexpr float rows_ns[2][2][5] = {{{0, 0.68f, 0.85f, 1.02f, 1.26f}, {0, 0.84f, 1.87f}},
+                                      {{0, 1.12f, 1.3f, 1.9f, 2.3f}, {0, 1.28f, 2.5f}}};
+  constexpr float ring_ps[2][2][5] = {{{0, 1.1f, 1.29f, 1.38f, 1.24f}, {0, 1.66f, 6.3f, 7.8f, 24.0f}},
+                                      {{0, 2.4f, 2.3f, 3.3f, 2.9f}, {0, 2.9f, 4.6f, 8.9f, 30.0f}}};
+  constexpr float ring_us[2][2][5] = {{{0, 9, 15, 25, 32}, {0, 10.5f, 42, 130, 255}},
+                                      {{0, 12, 19, 33, 38}, {0, 13, 40, 160, 340}}};
+  const double grids = 2048.0 / a.share;
+  // below fifteen rounds of waves the rows at any rate: the ring would save a tenth
+  // to a quarter there, but the count is an estimate (the others may be smaller) and
+  // the ring leaves the merged kernel (120 mixed FP64 grids: 560 us, 640 with the
+  // line at ten rounds, 861 with none)
+  const double width = c.NC == 1 ? 1.0 : c.NC == 2 ? 1.8 : 3.3;
+  if (grids * (double)c.waves * width < 30000.0) return true;
+  const double tiles = (double)((a.d1 + 31) / 32 * 32) * (double)((a.d2 + 63) / 64 * 64) * (double)a.d0;
+  const int t = es / 8, b = box ? 1 : 0;
+  const double rows = box && R >= 3 ? c.time : 4.0 + grids * (double)c.waves * width * rows_ns[t][b][R] * 1e-3;
+  return rows < 0.95 * (ring_us[t][b][R] + grids * tiles * ring_ps[t][b][R] * 1e-6);
 }
 
 // Whether the cut beats the plane ring: on ragged or misaligned grids always (the
@@ -369,9 +402,11 @@ inline Rows3DCut rows3d_best(const KArgs& a, int R, bool box, int es) {
 // 512^3.
 // Larger stars and 27-point boxes are bound by memory, where the ring reads a
 // plane once: 512^3 FP32 star 212-248 us against 311-690, 256^3 25-39 against 24-46.
+// Among 2048 / share grids like this one rows3d_better_many decides instead.
 template <typename T, int R, bool BOX>
 inline bool rows3d_better(const KArgs& a, const Rows3DCut& c) {
   if (!dma3d_ok<T>(a)) return true;
+  if (a.share > 0) return rows3d_better_many(a, c, R, BOX, (int)sizeof(T));
   const double pts = (double)a.d0 * (double)a.d1 * (double)a.d2;
   if (pts * sizeof(T) <= 32e6) return true;
   constexpr double ring_ps[2][2][5] = {{{0, 0, 4.9, 25.4, 48.3}, {0, 0, 9.7, 27.2, 82.5}},

@@ -75,3 +75,26 @@ def test_rows3d_batch_equals_alone():
     for got, w in zip(out, want):
         assert torch.equal(got, w)
     batch.close()
+
+
+# few and many grids of one size: the row gather of one column per lane, the plane
+# ring, and (boxes from order 3) the row gather of two or four columns
+@pytest.mark.parametrize("dtype", [st.F32, st.F64])
+@pytest.mark.parametrize("shape,r", [(st.STAR, 1), (st.STAR, 4), (st.BOX, 2), (st.BOX, 3), (st.BOX, 4)])
+@pytest.mark.parametrize("dims,count", [((16, 32, 64), 3), ((16, 32, 64), 150), ((21, 24, 104), 40), ((18, 21, 231), 20)])
+def test_rows3d_many_equals_alone(dtype, shape, r, dims, count):
+    torch = torch_cuda()
+    c = inputs.coefficients(3, r, shape, seed=90 + r, dtype=np.float64)
+    nd = np.float32 if dtype == st.F32 else np.float64
+    x0 = torch.stack([torch.from_numpy(inputs.grid(dims, seed=91 + k % 7, dtype=nd)) for k in range(count)]).cuda()
+    plan = st.Plan(dims, r, shape, c, boundary=st.BC_ZERO, dtype=dtype, path=st.PATH_GATHER, time_block=1)
+    b0, b1 = x0.clone(), torch.empty_like(x0)
+    batch = st.Batch([plan] * count, list(b0), list(b1))
+    out = (b0, b1)[batch.run_steps(2)].clone()
+    torch.cuda.synchronize()
+    batch.close()
+    plan.close()
+    for k in range(7 if count > 7 else count):
+        want = _one(torch, x0[k], r, shape, c, st.BC_ZERO, dtype)
+        for j in range(k, count, 7):
+            assert torch.equal(out[j], want), (k, j)
