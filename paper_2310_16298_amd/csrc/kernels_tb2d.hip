@@ -59,7 +59,7 @@ static int cut_rs2d(KArgs& a) {
 }
 
 // The LDS tiles (direct-to-LDS windows of 64 x 64, FP64 32 x 64) for a grid
-// alone that they suit better: orders 3 and 4 on grids in between, where the
+// alone that they suit better: orders 2 to 4 on grids in between, where the
 // pipeline's fill of 2 R steps rows is long against the chunks of a full
 // chip, and (FP64) its latency against 16-row tiles.  us per launch, LDS tiles
 // / register streaming: FP32 order-4 box 512^2 13.3 / 12.0, 1024^2 13.8 / 17.4,
@@ -67,7 +67,11 @@ static int cut_rs2d(KArgs& a) {
 // 1024^2 12.0 / 12.6, 1500^2 14.9 / 16.3, 2048^2 22.2 / 21.3; order-3 box 700^2 20.5 /
 // 19.0, 1024^2 20.6 / 23.4, 1500^2 34.9 / 35.2, 2500^2 69 / 62; FP64 order-4 star
 // 256^2 7.3 / 7.1, 512^2 7.1 / 8.2, 1024^2 11.7 / 11.9, 1500^2 17.5 / 16.0; order-4 box
-// 64^2 10.8 / 12.5, 512^2 9.9 / 21.5, 2048^2 53 / 68, 4096^2 190 / 172.
+// 64^2 10.8 / 12.5, 512^2 9.9 / 21.5, 2048^2 53 / 68, 4096^2 190 / 172; FP64 order 2
+// where one round of 16-row tiles takes the grid, zero halo: box 256^2 8.5 / 9.1,
+// 512^2 8.8 / 10.4, 48 x 4224 8.8 / 10.8, 768^2 14.2 / 11.6, star 384^2 6.8 / 7.0, 512^2 6.9 /
+// 7.8, 768^2 10.6 / 8.9 (periodic, whose windows wrap: box 48 x 4224 10.0 / 11.1, 512^2
+// 9.9 / 10.7, star 24 x 8448 8.4 / 9.3, 512^2 8.4 / 7.9).
 template <typename T, int R, bool BOX>
 static bool lds_tiles_better(const KArgs& a) {
   const int64_t pts = a.d0 * a.d1;
@@ -75,7 +79,9 @@ static bool lds_tiles_better(const KArgs& a) {
     return R == 4 ? (BOX ? pts >= 450000 && pts < 32000000 : pts >= 800000 && pts < 3000000)
                   : R == 3 && BOX && pts >= 800000 && pts < 2400000;
   else
-    return R == 4 && (BOX ? pts < 10000000 : pts >= 100000 && pts < 1100000);
+    return R == 4   ? (BOX ? pts < 10000000 : pts >= 100000 && pts < 1100000)
+           : R == 2 ? pts < 480000 && (a.periodic ? pts >= 180000 && (BOX || a.d0 < 32) : pts >= 45000)
+                    : false;
 }
 
 // MANY: the grid is one of many in a batched launch, whose items fill the chip

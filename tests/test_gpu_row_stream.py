@@ -59,3 +59,23 @@ def test_row_stream_values_not_finite(dtype, shape, bc):
         got = _advance(torch, x0, r, shape, c, bc, dtype, 2, 2)
         assert torch.equal(torch.nan_to_num(got, 7.0, 8.0, 9.0), torch.nan_to_num(want, 7.0, 8.0, 9.0))
         assert torch.equal(torch.isnan(got), torch.isnan(want))
+
+
+# FP64 order 2 on grids of one round of LDS tiles, against one step per launch
+@pytest.mark.parametrize("shape", [st.STAR, st.BOX])
+@pytest.mark.parametrize("dims,bc", [((250, 256), st.BC_ZERO), ((431, 448), st.BC_ZERO), ((17, 11264), st.BC_ZERO),
+                                     ((49, 4224), st.BC_PERIODIC), ((24, 8448), st.BC_PERIODIC)])
+def test_fp64_order2_tiles_equal_one_step(shape, dims, bc):
+    torch = torch_cuda()
+    c = inputs.coefficients(2, 2, shape, seed=61, dtype=np.float64)
+    x0 = torch.from_numpy(inputs.grid(dims, seed=62, dtype=np.float64)).cuda()
+    for steps in (2, 3, 4, 9):
+        outs = []
+        for tb in (1, 4):
+            plan = st.Plan(dims, 2, shape, c, boundary=bc, dtype=st.F64, path=st.PATH_GATHER, time_block=tb)
+            x = x0.clone()
+            y = torch.empty_like(x)
+            outs.append(plan.run_steps(x, y, steps).clone())
+            torch.cuda.synchronize()
+            plan.close()
+        assert torch.equal(outs[0], outs[1]), steps
