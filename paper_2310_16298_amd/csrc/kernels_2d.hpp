@@ -297,8 +297,11 @@ __global__ __launch_bounds__(kThreads) void mfma2d_kernel(KArgs a) {
   mfma2d_item<T, R, VAR>(a, xcd_remap(blockIdx.x, gridDim.x));
 }
 
+// FP64 of order 1 is held to 256 registers, two waves per SIMD: left to itself the
+// compiler takes 260 for the star's parallel lines, and one wave (256 grids of
+// 64^2, 128^2 and 256^2: 157, 146 and 151 GStencil/s at one wave, 197, 200 and 210 at two).
 template <typename T, int R, int VAR>
-__global__ __launch_bounds__(kThreads) void mfma2d_batch(BatchArgs b) {
+__global__ __launch_bounds__(kThreads, sizeof(T) == 8 && R == 1 ? 2 : 1) void mfma2d_batch(BatchArgs b) {
   for_each_batch_item(b, [&](const KArgs& x, int id) { mfma2d_item<T, R, VAR>(x, id); });
 }
 

@@ -1,0 +1,51 @@
+"""Registers of the built kernels: waves per SIMD that a kernel must not lose, read
+from the resource notes of the library's own code objects."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2310_16298_amd import build as hipbuild
+from paper_2310_16298_amd import stencil as st
+
+LLVM = os.path.join(os.path.dirname(hipbuild.HIPCC), "..", "llvm", "bin")
+
+
+@pytest.fixture(scope="module")
+def registers(tmp_path_factory):
+    """Mangled kernel name -> vector registers (accumulation registers included)."""
+    st.load_library()
+    tmp = tmp_path_factory.mktemp("kernels")
+    fat = str(tmp / "fat")
+    subprocess.run([os.path.join(LLVM, "llvm-objcopy"), "--dump-section", ".hip_fatbin=" + fat, hipbuild.LIB,
+                    str(tmp / "rest")], check=True)
+    data = open(fat, "rb").read()
+    at = [m.start() for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__|CCOB", data)] + [len(data)]
+    regs = {}
+    for k in range(len(at) - 1):
+        bundle, obj = str(tmp / f"bundle{k}"), str(tmp / f"obj{k}")
+        with open(bundle, "wb") as f:
+            f.write(data[at[k]:at[k + 1]])
+        res = subprocess.run([os.path.join(LLVM, "clang-offload-bundler"), "--type=o", "--unbundle", "--input=" + bundle,
+                              "--output=" + obj, "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], capture_output=True)
+        if res.returncode != 0 or not os.path.getsize(obj):
+            continue
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", obj], capture_output=True, text=True,
+                               check=True).stdout
+        for m in re.finditer(r"\.symbol:\s+'?([^\s']+)\.kd.*?\.vgpr_count:\s+(\d+)", notes, re.S):
+            regs[m.group(1)] = int(m.group(2))
+    assert len(regs) > 500
+    return regs
+
+
+def _of(registers, *parts):
+    found = {n: v for n, v in registers.items() if all(p in n for p in parts)}
+    assert found, parts
+    return found
+
+
+def test_batched_fp64_order1_outer_products_run_two_waves(registers):
+    # 512 vector registers per SIMD lane
+    for name, v in _of(registers, "mfma2d_batchIdLi1E").items():
+        assert v <= 256, (name, v)
