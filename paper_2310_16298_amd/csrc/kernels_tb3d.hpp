@@ -339,8 +339,13 @@ struct Tb3Stream {
   static_assert(R <= 4, "level-1 blocks k0 - 4 .. cover the level-2 reach");
 };
 
+// Weights in vector registers up to order 2.  The stars of order 3 and 4 have none
+// to spare: order 3 went from 242 to 269, from two waves per SIMD to one (us a
+// launch, scalar / vector: 256^3 101 / 137, 384^3 249 / 440, 512^3 524 / 852), order 4 from 292 to
+// 327 (384^3 494 / 560, 512^3 938 / 1072).
 template <typename T, int R, bool BOX>
 __device__ __forceinline__ void tb3d_stream_item(const KArgs& a, int item) {
+  constexpr bool VW = R <= 2;
   typedef Tb3Stream<T, R, BOX> S;
   typedef typename S::D D;
   typedef typename Tb3Vec<T>::type V;
@@ -407,7 +412,7 @@ __device__ __forceinline__ void tb3d_stream_item(const KArgs& a, int item) {
           for (int ap = 0; ap < W; ++ap)
 #pragma unroll
             for (int cc = 0; cc < W; ++cc) {
-              const T wgt = vector_weight<T>(c[(ap * W + bb) * W + cc]);
+              const T wgt = vector_weight<T, VW>(c[(ap * W + bb) * W + cc]);
 #pragma unroll
               for (int e = 0; e < 4; ++e) ring[2 * R - ap][p][e] += wgt * v[4 - R + e + cc];
             }
@@ -423,7 +428,7 @@ __device__ __forceinline__ void tb3d_stream_item(const KArgs& a, int item) {
         for (int p = 0; p < 2; ++p) {
           const int bb = x - p;
           if (bb < 0 || bb > 2 * R) continue;
-          const T wgt = vector_weight<T>(c[(R * W + bb) * W + R]);
+          const T wgt = vector_weight<T, VW>(c[(R * W + bb) * W + R]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) ring[R][p][e] += wgt * v[4 + e];
         }
@@ -436,14 +441,14 @@ __device__ __forceinline__ void tb3d_stream_item(const KArgs& a, int item) {
 #pragma unroll
         for (int cc = 0; cc < W; ++cc) {
           if (cc == R) continue;
-          const T wgt = vector_weight<T>(c[(R * W + R) * W + cc]);
+          const T wgt = vector_weight<T, VW>(c[(R * W + R) * W + cc]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) ring[R][p][e] += wgt * v[4 - R + e + cc];
         }
 #pragma unroll
         for (int ap = 0; ap < W; ++ap) {
           if (ap == R) continue;
-          const T wgt = vector_weight<T>(c[(ap * W + R) * W + R]);
+          const T wgt = vector_weight<T, VW>(c[(ap * W + R) * W + R]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) ring[2 * R - ap][p][e] += wgt * v[4 + e];
         }

@@ -49,3 +49,10 @@ def test_batched_fp64_order1_outer_products_run_two_waves(registers):
     # 512 vector registers per SIMD lane
     for name, v in _of(registers, "mfma2d_batchIdLi1E").items():
         assert v <= 256, (name, v)
+
+
+def test_two_step_stream_of_order_3_runs_two_waves(registers):
+    for name, v in _of(registers, "tb3d_stream_kernelIfLi3E").items():
+        assert v <= 256, (name, v)
+    for name, v in _of(registers, "tb3d_stream_kernelIfLi4E").items():
+        assert v <= 300, (name, v)  # one wave; vector weights took 327
