@@ -339,13 +339,15 @@ struct Tb3Stream {
   static_assert(R <= 4, "level-1 blocks k0 - 4 .. cover the level-2 reach");
 };
 
-// Weights in vector registers up to order 2.  The stars of order 3 and 4 have none
-// to spare: order 3 went from 242 to 269, from two waves per SIMD to one (us a
-// launch, scalar / vector: 256^3 101 / 137, 384^3 249 / 440, 512^3 524 / 852), order 4 from 292 to
-// 327 (384^3 494 / 560, 512^3 938 / 1072).
-template <typename T, int R, bool BOX>
+// VW: weights in vector registers, for a grid alone up to order 2.  The stars of
+// order 3 and 4 have none to spare: order 3 went from 242 to 269, from two waves
+// per SIMD to one (us a launch, scalar / vector: 256^3 101 / 137, 384^3 249 / 440, 512^3
+// 524 / 852), order 4 from 292 to 327 (384^3 494 / 560, 512^3 938 / 1072).  Batched, the
+// order-2 star and the 27-point box pass 128 and a CU takes one workgroup less
+// (us a step: star, three grids of 320^3 148 / 244, four of 64 x 512 x 512 114 / 193; box, the
+// latter 131 / 179).
+template <typename T, int R, bool BOX, bool VW>
 __device__ __forceinline__ void tb3d_stream_item(const KArgs& a, int item) {
-  constexpr bool VW = R <= 2;
   typedef Tb3Stream<T, R, BOX> S;
   typedef typename S::D D;
   typedef typename Tb3Vec<T>::type V;
@@ -556,12 +558,12 @@ __device__ __forceinline__ void tb3d_stream_item(const KArgs& a, int item) {
 
 template <typename T, int R, bool BOX>
 __global__ __launch_bounds__((Tb3Stream<T, R, BOX>::NT)) void tb3d_stream_kernel(KArgs a) {
-  tb3d_stream_item<T, R, BOX>(a, xcd_remap(blockIdx.x, gridDim.x));
+  tb3d_stream_item<T, R, BOX, (R <= 2)>(a, xcd_remap(blockIdx.x, gridDim.x));
 }
 
 template <typename T, int R, bool BOX>
 __global__ __launch_bounds__((Tb3Stream<T, R, BOX>::NT)) void tb3d_stream_batch(BatchArgs b) {
-  for_each_batch_item(b, [&](const KArgs& x, int id) { tb3d_stream_item<T, R, BOX>(x, id); });
+  for_each_batch_item(b, [&](const KArgs& x, int id) { tb3d_stream_item<T, R, BOX, false>(x, id); });
 }
 
 }  // namespace stencil

@@ -56,3 +56,10 @@ def test_two_step_stream_of_order_3_runs_two_waves(registers):
         assert v <= 256, (name, v)
     for name, v in _of(registers, "tb3d_stream_kernelIfLi4E").items():
         assert v <= 300, (name, v)  # one wave; vector weights took 327
+
+
+def test_batched_two_step_stream_fits_its_workgroups(registers):
+    # 5 and 6 waves a workgroup: a CU takes one less past 128 registers
+    for part in ("IfLi2ELb0E", "IfLi1ELb1E"):
+        for name, v in _of(registers, "tb3d_stream_batch" + part).items():
+            assert v <= 128, (name, v)
