@@ -58,33 +58,47 @@ static int cut_rs2d(KArgs& a) {
   return best;
 }
 
+// Few rows and many columns: the walk's chunks shrink to a row or two there, each
+// with a pipeline fill of its own.
+static bool wide(const KArgs& a) { return a.d0 >= 16 && a.d1 > 64 * a.d0; }
+
 // The LDS tiles (direct-to-LDS windows of 64 x 64, FP64 32 x 64) for a grid
 // alone that they suit better: orders 2 to 4 on grids in between, where the
 // pipeline's fill of 2 R steps rows is long against the chunks of a full
-// chip, and (FP64) its latency against 16-row tiles.  us per launch, LDS tiles
-// / register streaming: FP32 order-4 box 512^2 13.3 / 12.0, 1024^2 13.8 / 17.4,
+// chip, and (FP64) its latency against 16-row tiles.  The tiles stage a zero halo
+// faster than a periodic one, whose windows wrap.  us per launch, LDS tiles
+// / register streaming, periodic: FP32 order-4 box 512^2 13.3 / 12.0, 1024^2 13.8 / 17.4,
 // 2048^2 27 / 37, 4096^2 81 / 94, 6144^2 184 / 174; order-4 star 700^2 11.9 / 10.6,
 // 1024^2 12.0 / 12.6, 1500^2 14.9 / 16.3, 2048^2 22.2 / 21.3; order-3 box 700^2 20.5 /
 // 19.0, 1024^2 20.6 / 23.4, 1500^2 34.9 / 35.2, 2500^2 69 / 62; FP64 order-4 star
 // 256^2 7.3 / 7.1, 512^2 7.1 / 8.2, 1024^2 11.7 / 11.9, 1500^2 17.5 / 16.0; order-4 box
-// 64^2 10.8 / 12.5, 512^2 9.9 / 21.5, 2048^2 53 / 68, 4096^2 190 / 172; FP64 order 2
-// where one round of 16-row tiles takes the grid, zero halo: box 256^2 8.5 / 9.1,
+// 64^2 10.8 / 12.5, 512^2 9.9 / 21.5, 2048^2 53 / 68, 4096^2 190 / 172.  Zero halo: FP32
+// order-4 box 384^2 12.2 / 11.0, 512^2 12.2 / 12.6, 640^2 12.6 / 13.8, 24 x 8448 12.0 / 13.0;
+// order-4 star 640^2 10.7 / 10.8, 768^2 10.7 / 11.4, 2048^2 20.0 / 22.2, 2560^2 29.8 / 27.3; order-3
+// star 768^2 12.2 / 11.2, 1024^2 12.5 / 13.2, 1280^2 14.9 / 15.2; FP64 order-4 star 64^2 5.6 / 6.8,
+// 256^2 5.9 / 7.8, 1280^2 12.6 / 13.6, 2048^2 23.1 / 21.6; order-3 star 384^2 6.2 / 6.0, 512^2 6.4 / 6.6,
+// 24 x 8448 6.8 / 7.6, 768^2 9.3 / 7.6.  FP64 order 2, zero halo: box 256^2 8.5 / 9.1,
 // 512^2 8.8 / 10.4, 48 x 4224 8.8 / 10.8, 768^2 14.2 / 11.6, star 384^2 6.8 / 7.0, 512^2 6.9 /
-// 7.8, 768^2 10.6 / 8.9 (periodic, whose windows wrap: box 48 x 4224 10.0 / 11.1, 512^2
-// 9.9 / 10.7, star 24 x 8448 8.4 / 9.3, 512^2 8.4 / 7.9).
+// 7.8, 768^2 10.6 / 8.9; periodic: box 48 x 4224 10.0 / 11.1, 512^2 9.9 / 10.7, star 24 x 8448
+// 8.4 / 9.3, 48 x 4224 9.1 / 9.6, 128 x 2048 9.3 / 9.2, 512^2 9.0 / 8.4.
 template <typename T, int R, bool BOX>
 static bool lds_tiles_better(const KArgs& a) {
   const int64_t pts = a.d0 * a.d1;
-  if constexpr (sizeof(T) == 4)
-    return R == 4 ? (BOX ? pts >= 450000 && pts < 32000000 : pts >= 800000 && pts < 3000000)
-                  : R == 3 && BOX && pts >= 800000 && pts < 2400000;
-  else
-    return R == 4   ? (BOX ? pts < 10000000 : pts >= 100000 && pts < 1100000)
-           : R == 2 ? pts < 480000 && (a.periodic ? pts >= 180000 && (BOX || a.d0 < 32) : pts >= 45000)
-                    : false;
+  if constexpr (sizeof(T) == 4) {
+    if (BOX && R == 4)
+      return pts < 32000000 && pts >= (a.periodic || a.d0 < 16 ? 450000 : wide(a) ? 100000 : 250000);
+    if (R == 4) return a.periodic ? pts >= 800000 && pts < 3000000 : pts >= 500000 && pts < 6000000;
+    if (BOX && R == 3) return pts >= 800000 && pts < 2400000;
+    return R == 3 && !a.periodic && pts >= 800000 && pts < 1700000;
+  } else {
+    if (BOX && R == 4) return pts < 10000000;
+    if (R == 4) return a.periodic ? pts >= 100000 && pts < 1100000 : pts < 2000000;
+    if (R == 3) return !BOX && !a.periodic && a.d0 >= 16 && pts > 200000 && pts < 450000;
+    return R == 2 && pts < 480000 && (a.periodic ? pts >= 180000 && (BOX || wide(a)) : pts >= 45000);
+  }
 }
 
-// MANY: the grid is one of many in a batched launch, whose items fill the chip
+// MANY: the grid is one of many in a batched launch.
 template <typename T, int R, bool BOX, bool MANY = false>
 static Kernel pick_tb2d(KArgs& a, int32_t chunk) {
   // a launch of one step (the remainder of a run): the one-step gather
