@@ -98,18 +98,42 @@ static bool lds_tiles_better(const KArgs& a) {
   }
 }
 
+// Among many grids the tiles win where all of the class's grids together are about
+// one round of waves: the walk's chunks are as short as their fill then, and
+// there are too few of them to hide it (us a step, tiles / walk, zero halo: 16 FP32 grids
+// of 256^2, stars r = 2..4 3.1 / 3.5, 3.7 / 4.7, 4.5 / 6.1, boxes r = 3, 4 6.1 / 7.1, 8.3 / 10.7;
+// 64 of 256^2 6.8 / 4.3, 11.7 / 6.3, 14.0 / 8.3, 21.3 / 13.3, 27.9 / 20.1; two FP64 ones of 512^2,
+// stars 2.7 / 3.4, 4.6 / 5.8, 4.4 / 6.8, order-2 box 3.3 / 4.1; eight 5.8 / 4.6, 9.6 / 7.3, 9.1 / 9.2,
+// 7.8 / 5.9; 50 FP32 order-4 stars of 96^2 4.1 / 4.6, four of 128^2 3.8 / 3.8).
+template <typename T, int R, bool BOX>
+static bool lds_tiles_better_many(const KArgs& a) {
+  const double total = (double)a.d0 * (double)a.d1 * 2048.0 / a.share;  // points of the class
+  if (total >= 1.6e6) return false;
+  if constexpr (sizeof(T) == 4) {
+    if (R == 4) return a.d1 > 64 ? total >= (a.periodic ? 5.0e5 : 4.0e5) : !BOX && total >= 7.0e5;
+    return a.d1 > 64 && total >= (R == 3 && !BOX && !a.periodic ? 5.0e5 : 7.0e5);
+  } else {
+    if (BOX && R == 4) return false;
+    if (R == 4 && !a.periodic) return true;
+    if (R == 4) return a.d1 >= 256 && total >= 5.0e5;
+    return a.d1 >= 512 && total >= 5.0e5 && total < 1.0e6;
+  }
+}
+
 // MANY: the grid is one of many in a batched launch.
 template <typename T, int R, bool BOX, bool MANY = false>
 static Kernel pick_tb2d(KArgs& a, int32_t chunk) {
   // a launch of one step (the remainder of a run): the one-step gather
   if (a.steps <= 1) return find_gather2d(std::is_same<T, double>::value ? STENCIL_F64 : STENCIL_F32, R, BOX)(a, chunk);
-  if constexpr (!MANY && tb2d_dma_built<T>(R, BOX)) {
-    if (tb2d_fast<T>(a) && a.zeros != nullptr && lds_tiles_better<T, R, BOX>(a)) {
+  if constexpr (tb2d_dma_built<T>(R, BOX)) {
+    if (tb2d_fast<T>(a) && a.zeros != nullptr &&
+        (MANY ? lds_tiles_better_many<T, R, BOX>(a) : lds_tiles_better<T, R, BOX>(a))) {
       int TM = TbDmaShape<T, R, 2>::TM;
       a.tiles1 = (int32_t)((a.d1 + 63) / 64);
       // FP64 grids of fewer tiles than CUs (launch-bound: 512^2 has 128) take
       // 16-row tiles, twice the workgroups at the cost of more halo rows
-      const bool small = !std::is_same<T, float>::value && (int64_t)((a.d0 + TM - 1) / TM) * a.tiles1 < 256;
+      const bool small =
+          !MANY && !std::is_same<T, float>::value && (int64_t)((a.d0 + TM - 1) / TM) * a.tiles1 < 256;
       if (small) TM = kTbSmallRows;
       a.tiles0 = (int32_t)((a.d0 + TM - 1) / TM);
       return tb2d_dma<T, BOX>(R, a.steps, (int64_t)a.tiles0 * a.tiles1, small);

@@ -207,13 +207,18 @@ __global__ __launch_bounds__(256) void tb2d_dma_kernel(KArgs a) {
   tb2d_dma_item<T, R, BOX, TS, TM_>(a, xcd_remap(blockIdx.x, gridDim.x));
 }
 
+template <typename T, int R, bool BOX, int TS>
+__global__ __launch_bounds__(256) void tb2d_dma_batch(BatchArgs b) {
+  for_each_batch_item(b, [&](const KArgs& x, int id) { tb2d_dma_item<T, R, BOX, TS>(x, id); });
+}
+
 constexpr int kTbSmallRows = 16;  // FP64 tile rows on grids of fewer tiles than CUs
 
 // Orders with tiles, and the kernel of `steps` steps (FP32: 2 .. 4 at orders 2 and 3, 2 .. 3
-// at order 4; FP64: 2 .. 4 at order 2, else 2); single-grid launches only.
+// at order 4; FP64: 2 .. 4 at order 2, else 2); small tiles in single-grid launches only.
 template <typename T>
 constexpr bool tb2d_dma_built(int R, bool box) {
-  return R == 4 || (sizeof(T) == 4 ? R == 3 : R == 2 || (R == 3 && !box));
+  return R == 4 || (sizeof(T) == 4 ? R == 3 || (R == 2 && !box) : R == 2 || (R == 3 && !box));
 }
 template <typename T, bool BOX>
 Kernel tb2d_dma(int R, int steps, int64_t items, bool small_tiles);

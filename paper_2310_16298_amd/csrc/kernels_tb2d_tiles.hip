@@ -5,7 +5,7 @@ namespace stencil {
 
 template <typename T, int R, bool BOX, int TS>
 static Kernel tiles(int64_t items) {
-  return kernel_of<tb2d_dma_kernel<T, R, BOX, TS>>(items);
+  return kernel_of<tb2d_dma_kernel<T, R, BOX, TS>, tb2d_dma_batch<T, R, BOX, TS>>(items);
 }
 
 // steps 2 .. 4, or 2 .. 3 at order 4
@@ -25,7 +25,9 @@ Kernel tb2d_dma<float, true>(int R, int steps, int64_t items, bool) {
 
 template <>
 Kernel tb2d_dma<float, false>(int R, int steps, int64_t items, bool) {
-  return R == 3 ? tiles_of<float, 3, false>(steps, items) : tiles_of<float, 4, false>(steps, items);
+  return R == 2   ? tiles_of<float, 2, false>(steps, items)
+         : R == 3 ? tiles_of<float, 3, false>(steps, items)
+                  : tiles_of<float, 4, false>(steps, items);
 }
 
 template <int R, bool BOX, int TS>

@@ -1,6 +1,6 @@
 """The time-blocked 2D gather on LDS tiles, inside the sizes where it is chosen:
-grids alone, every step count, remainders of tiles, both boundaries, bit for bit
-against one step per launch, and against the oracle."""
+grids alone (every step count, remainders of tiles, both boundaries) and classes
+of a batch, bit for bit against one step per launch, and against the oracle."""
 import numpy as np
 import pytest
 
@@ -61,3 +61,36 @@ def test_tiles_alone(dims, r, shape, bc, dtype, tmax):
     bound = error_bound(ce, 2, r, shape, dtype, st.PATH_GATHER, steps, float(np.abs(a0).max()))
     assert float(np.abs(got.cpu().numpy() - want).max()) <= bound
 
+
+# classes of about one round of waves
+BATCH = [((250, 252), 16, 2, st.STAR, st.F32), ((250, 252), 16, 3, st.STAR, st.F32), ((250, 252), 16, 4, st.STAR, st.F32),
+         ((250, 252), 16, 3, st.BOX, st.F32), ((250, 252), 16, 4, st.BOX, st.F32), ((61, 64), 256, 4, st.STAR, st.F32),
+         ((518, 516), 2, 2, st.STAR, st.F64), ((518, 516), 2, 2, st.BOX, st.F64), ((518, 516), 2, 3, st.STAR, st.F64),
+         ((518, 516), 2, 4, st.STAR, st.F64)]
+
+
+@pytest.mark.parametrize("bc", [Z, P])
+@pytest.mark.parametrize("dims,count,r,shape,dtype", BATCH)
+def test_tiles_in_a_batch(dims, count, r, shape, dtype, bc):
+    torch = torch_cuda()
+    c = inputs.coefficients(2, r, shape, seed=310 + r, dtype=np.float64)
+    seeds = [311 + k % 5 for k in range(count)]
+    plan = st.Plan(dims, r, shape, c, boundary=bc, dtype=dtype)
+    T = plan.info["time_block"]
+    assert T > 1
+    b0 = torch.stack([torch.from_numpy(_grid(dims, s, dtype)) for s in seeds]).cuda()
+    x0 = b0.clone()
+    b1 = torch.empty_like(b0)
+    batch = st.Batch([plan] * count, list(b0), list(b1))
+    names = launched(torch, lambda: batch.run_steps(2 * T))
+    assert any("tb2d_dma_batch" in n for n in names), names
+    for steps in range(2, T + 3):
+        b0.copy_(x0)
+        out = (b0, b1)[batch.run_steps(steps)]
+        torch.cuda.synchronize()
+        for k in range(min(count, 5)):
+            want = _run(torch, _grid(dims, seeds[k], dtype), r, shape, c, bc, dtype, 1, steps)
+            for j in range(k, count, 5):
+                assert torch.equal(out[j], want), (steps, j)
+    batch.close()
+    plan.close()
