@@ -202,6 +202,13 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       const int nc = rs2d_batch_cut(grids, share.data(), m.second.data());
       for (int32_t i : m.second) columns[i] = nc;
     }
+    // one-step gathers of all taps merge by type and dimension
+    std::map<std::pair<int, int>, std::set<int>> mergeable;
+    for (int32_t i = 0; i < count; ++i) {
+      const Resolved& rs = plans[i]->rs;
+      if ((rs.family == FAM_GATHER2D || rs.family == FAM_GATHER3D || rs.family == FAM_TB3D) && rs.frag.empty())
+        mergeable[{rs.info.ndim, rs.info.dtype}].insert(2 * rs.info.radius + (rs.info.shape != STENCIL_STAR ? 1 : 0));
+    }
     for (int32_t i = 0; i < count; ++i) {
       const Resolved& rs = plans[i]->rs;
       const int T = rs.tb_auto ? rs.time_block : 1;
@@ -243,7 +250,8 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       if (placed) continue;
       plain.emplace_back();
       plain.back().flops = rs.info.executed_flops_per_point;
-      plain.back().k = plan_kernel(rs, buf0[i], buf1[i], &plain.back().a, 1, nullptr, columns[i], share[i]);
+      plain.back().k = plan_kernel(rs, buf0[i], buf1[i], &plain.back().a, 1, nullptr, columns[i], share[i],
+                                   (int)mergeable[{rs.info.ndim, rs.info.dtype}].size());
       if (!plain.back().k.launch || plain.back().k.items < 1) {
         delete b;
         return STENCIL_EINTERNAL;

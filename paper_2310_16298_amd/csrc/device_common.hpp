@@ -41,7 +41,7 @@ struct KArgs {
   int32_t share;        // host only: 0 = alone in its launch, else the grid's share of the launch's waves
   int32_t columns;      // host only: columns per lane of the batch's 2D gather class, 0 = free
   int32_t variant;      // merged batched kernels: 2 order + (box ? 1 : 0)
-  int32_t pad;
+  int32_t kinds;        // host only: stencils whose one-step gathers merge in the launch, with this one
 };
 
 // Pointer to data that no lane writes during a kernel (constant address

@@ -89,7 +89,7 @@ static bool lds_tiles_better(const KArgs& a) {
       return pts < 32000000 && pts >= (a.periodic || a.d0 < 16 ? 450000 : wide(a) ? 100000 : 250000);
     if (R == 4) return a.periodic ? pts >= 800000 && pts < 3000000 : pts >= 500000 && pts < 6000000;
     if (BOX && R == 3) return pts >= 800000 && pts < 2400000;
-    return R == 3 && !a.periodic && pts >= 800000 && pts < 1700000;
+    return R == 3 && !a.periodic && a.d1 > 64 && pts >= 800000 && pts < 1700000;
   } else {
     if (BOX && R == 4) return pts < 10000000;
     if (R == 4) return a.periodic ? pts >= 100000 && pts < 1100000 : pts < 2000000;

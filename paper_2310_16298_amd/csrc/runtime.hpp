@@ -119,12 +119,14 @@ inline stencil_status_t check_device(int device) {
 
 // The resolved plan's args with the two buffers and the launch's step count
 // filled in, its kernel picked (by `pick`, else the plan's own picker) and the
-// decomposition applied.  share > 0: one of several grids in a launch.
+// decomposition applied.  share > 0: one of several grids in a launch, kinds: of
+// stencils whose one-step gathers merge there.
 inline Kernel plan_kernel(const Resolved& rs, const void* in, void* out, KArgs* a, int fused = 1,
-                          Picker pick = nullptr, int columns = 0, int share = 0) {
+                          Picker pick = nullptr, int columns = 0, int share = 0, int kinds = 0) {
   *a = rs.args;
   a->columns = columns;
   a->share = share;
+  a->kinds = kinds;
   a->in = in;
   a->out = out;
   a->steps = fused;

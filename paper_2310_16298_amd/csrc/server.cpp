@@ -232,6 +232,7 @@ stencil_status_t admit(stencil_server_s* s, Request* r) {
   a.in = b0;
   a.out = b1;
   a.share = 512;  // one of several grids in a launch: a quarter of a full launch's waves
+  a.kinds = 2;    // requests of several stencils, whose one-step gathers merge
   r->kernel = r->rs.pick(a, r->rs.chunk_req);
   if (!r->kernel.launch_batch || r->kernel.items < 1) return STENCIL_EINTERNAL;
   r->args = a;
