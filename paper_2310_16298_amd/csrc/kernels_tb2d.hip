@@ -77,7 +77,7 @@ static bool wide(const KArgs& a) { return a.d0 >= 16 && a.d1 > 64 * a.d0; }
 // order-4 star 640^2 10.7 / 10.8, 768^2 10.7 / 11.4, 2048^2 20.0 / 22.2, 2560^2 29.8 / 27.3; order-3
 // star 768^2 12.2 / 11.2, 1024^2 12.5 / 13.2, 1280^2 14.9 / 15.2; FP64 order-4 star 64^2 5.6 / 6.8,
 // 256^2 5.9 / 7.8, 1280^2 12.6 / 13.6, 2048^2 23.1 / 21.6; order-3 star 384^2 6.2 / 6.0, 512^2 6.4 / 6.6,
-// 24 x 8448 6.8 / 7.6, 768^2 9.3 / 7.6.  FP64 order 2, zero halo: box 256^2 8.5 / 9.1,
+// 24 x 8448 6.8 / 7.6, 768^2 9.3 / 7.6, 40000 x 8 15 / 11.  FP64 order 2, zero halo: box 256^2 8.5 / 9.1,
 // 512^2 8.8 / 10.4, 48 x 4224 8.8 / 10.8, 768^2 14.2 / 11.6, star 384^2 6.8 / 7.0, 512^2 6.9 /
 // 7.8, 768^2 10.6 / 8.9; periodic: box 48 x 4224 10.0 / 11.1, 512^2 9.9 / 10.7, star 24 x 8448
 // 8.4 / 9.3, 48 x 4224 9.1 / 9.6, 128 x 2048 9.3 / 9.2, 512^2 9.0 / 8.4.
@@ -93,7 +93,7 @@ static bool lds_tiles_better(const KArgs& a) {
   } else {
     if (BOX && R == 4) return pts < 10000000;
     if (R == 4) return a.periodic ? pts >= 100000 && pts < 1100000 : pts < 2000000;
-    if (R == 3) return !BOX && !a.periodic && a.d0 >= 16 && pts > 200000 && pts < 450000;
+    if (R == 3) return !BOX && !a.periodic && a.d0 >= 16 && a.d1 > 64 && pts > 200000 && pts < 450000;
     return R == 2 && pts < 480000 && (a.periodic ? pts >= 180000 && (BOX || wide(a)) : pts >= 45000);
   }
 }

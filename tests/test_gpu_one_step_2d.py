@@ -121,3 +121,14 @@ def test_many_of_one_stencil(dtype, r, shape, bc, dims, count, kernel):
         for j in range(k, count, 7):
             assert torch.equal(out[j], want), j
     plan.close()
+
+
+def test_one_strip_of_many_rows_takes_the_walk():
+    torch = torch_cuda()
+    c = inputs.coefficients(2, 3, S, seed=440, dtype=np.float64)
+    plan = st.Plan((40000, 8), 3, S, c, boundary=Z, dtype=D)
+    x, y = _two(torch, _grid((40000, 8), 441, D), 0)
+    assert plan.info["time_block"] == 2
+    names = launched(torch, lambda: plan.run_steps(x, y, 2))
+    plan.close()
+    assert len(names) == 1 and "rs2d_kernel" in names[0], names
