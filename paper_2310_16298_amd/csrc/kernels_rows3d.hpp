@@ -20,7 +20,10 @@
 // 111 / 231 / 504.
 #pragma once
 
+#include <cmath>
+
 #include "dma3d.hpp"
+#include "kernels_3d.hpp"
 #include "kernels_rs2d.hpp"
 
 namespace stencil {
@@ -368,32 +371,94 @@ inline Rows3DCut rows3d_best(const KArgs& a, int R, bool box, int es) {
   return best;
 }
 
+// Plane-tiles of the ring kernels (plane ring and n = 4 outer products) over the grids
+// of a class: workgroups on the fullest CU, and thousands of 32 x 64 tiles filled
+// by the grid in the planes a chunk walks, its 2R warm-up planes included.
+struct RingLoad {
+  double rounds = 0.0, planes = 0.0;
+};
+
+inline RingLoad ring_load(const KArgs& a, int R) {
+  const double grids = a.share > 0 ? 2048.0 / a.share : 1.0;
+  RingLoad l;
+  l.rounds = std::ceil(grids * (double)chunk3d_items(a) / 256.0);
+  l.planes = grids * (double)a.nchunks * (a.chunk + 2 * R) * (double)(a.d1 * a.d2) / 2048.0e3;
+  return l;
+}
+
+// us a step of the grids of a class (2048 / share of them) on the rows: fitted to
+// batches of 1 .. 2048 grids of 16^3 .. 256^3 by waves of one column and four
+// rows; boxes of order 4, and FP64 ones of order 3, by the cut's own time.
+inline double rows3d_many_us(const KArgs& a, const Rows3DCut& c, int R, bool box, int es) {
+  constexpr double k[2][2][5][2] = {
+      {{{0, 0}, {4.4, 0.648}, {4.7, 0.834}, {4.8, 1.04}, {5.1, 1.26}}, {{0, 0}, {4.6, 0.803}, {5.8, 1.81}, {7.6, 3.9}}},
+      {{{0, 0}, {4.5, 0.904}, {4.8, 1.227}, {4.8, 1.83}, {5.0, 2.2}}, {{0, 0}, {4.8, 1.084}, {6.5, 2.29}}}};
+  if (box && R == 4) return es == 4 ? 1.1 + 0.953 * c.time : 5.4 + 1.003 * c.time;
+  if (box && R == 3 && es == 8) return 2.5 + 1.028 * c.time;
+  const double* f = k[es / 8][box ? 1 : 0][R];
+  const double width = (c.NC == 1 ? 1.0 : c.NC == 2 ? 1.8 : 3.3) * c.J / 4.0;
+  return f[0] + f[1] * (2048.0 / a.share) * (double)c.waves * width * 1e-3;
+}
+
+// The same on the plane ring and on the FP32 outer products of order 3 and 4.
+inline double ring3d_many_us(const RingLoad& l, int R, bool box, int es) {
+  constexpr double k[2][2][5][3] = {
+      {{{0, 0, 0}, {7.2, 1.28, 1.22}, {12.7, 2.38, 1.19}, {19.5, 4.75, 0.73}, {26.3, 7.5, 0.86}},
+       {{0, 0, 0}, {8.3, 2.52, 0.82}, {23.2, 14.3, 0.57}, {63.8, 57.2, 0}, {64.1, 199, 6.9}}},
+      {{{0, 0, 0}, {8.1, 2.8, 2.27}, {13.2, 4.6, 2.5}, {18.2, 14.8, 1.2}, {24.5, 13.2, 2.1}},
+       {{0, 0, 0}, {8.7, 4.5, 1.54}, {15.2, 25.2, 1.6}, {67, 97.7, 0}, {47.7, 341, 9.2}}}};
+  const double* f = k[es / 8][box ? 1 : 0][R];
+  return f[0] + f[1] * l.rounds + f[2] * l.planes;
+}
+inline double mfma3d_box_many_us(const RingLoad& l, int R) {
+  return R == 3 ? 38.7 + 59.9 * l.rounds + 1.0 * l.planes : 67.3 + 148.9 * l.rounds + 3.5 * l.planes;
+}
+
 // One of many aligned grids: the rows end early (a chip's waves of them in 5-25 us),
-// the ring's few deep items late (8-400 us, ring_us) but at less cost a point, so
-// the rows serve few or small grids and the ring many.  Estimates in us from
-// batches of 4 .. 1024 grids of 24^3 .. 96^3: rows_ns a wave of one column and
-// four rows (boxes from order 3: the cut's estimate); ring_ps a point of the 32 x 64
-// tiles.  Ring / rows, us a step: FP32 order-3 star 32^3 x 16 24.9 / 8.9, x 64 26.4 /
-// 19.9, x 256 40 / 77, x 1024 117 / 268, 64^3 x 16 29 / 20, x 64 41 / 66; order-3 box
-// 48^3 x 64 224 / 156, 32^3 x 256 265 / 279; FP64 order-4 star 64^3 x 64 61 / 140.
+// the ring's few deep items late but at less cost a point, so the rows serve few
+// or small grids and the ring many.  Ring / rows, us a step: FP32 7-point star 32^3
+// x 16 8.3 / 7.1, x 64 10.5 / 13.5, 64^3 x 4 9.4 / 7.2, x 16 12.0 / 14.4, 128^3 x 2 12.5 / 18.4; order-3
+// star 32^3 x 64 24 / 20, x 256 33 / 76; order-2 box 32^3 x 128 48 / 64, 24^3 x 128 45 / 36; order-3 box
+// 48^3 x 64 164 / 157, 32^3 x 256 236 / 281; FP64 27-point box 128^3 x 2 22 / 29, order-4 box 32^3 x 64 363 /
+// 188, x 256 718 / 747; 24^3 x 1024 2800 / 1556.
+// Beside other stencils of its type the rows also share a launch: there they are
+// taken below fifteen rounds of waves at any rate, as the ring would save a tenth to
+// a quarter and leave the merged kernel (120 mixed FP64 grids: 560 us, 640 with the
+// line at ten rounds, 861 with none).
 inline bool rows3d_better_many(const KArgs& a, const Rows3DCut& c, int R, bool box, int es) {
-  constexpr float rows_ns[2][2][5] = {{{0, 0.68f, 0.85f, 1.02f, 1.26f}, {0, 0.84f, 1.87f}},
-                                      {{0, 1.12f, 1.3f, 1.9f, 2.3f}, {0, 1.28f, 2.5f}}};
-  constexpr float ring_ps[2][2][5] = {{{0, 1.1f, 1.29f, 1.38f, 1.24f}, {0, 1.66f, 6.3f, 7.8f, 24.0f}},
-                                      {{0, 2.4f, 2.3f, 3.3f, 2.9f}, {0, 2.9f, 4.6f, 8.9f, 30.0f}}};
-  constexpr float ring_us[2][2][5] = {{{0, 9, 15, 25, 32}, {0, 10.5f, 42, 130, 255}},
-                                      {{0, 12, 19, 33, 38}, {0, 13, 40, 160, 340}}};
-  const double grids = 2048.0 / a.share;
-  // below fifteen rounds of waves the rows at any rate: the ring would save a tenth
-  // to a quarter there, but the count is an estimate (the others may be smaller) and
-  // the ring leaves the merged kernel (120 mixed FP64 grids: 560 us, 640 with the
-  // line at ten rounds, 861 with none)
   const double width = c.NC == 1 ? 1.0 : c.NC == 2 ? 1.8 : 3.3;
-  if (grids * (double)c.waves * width < 30000.0) return true;
-  const double tiles = (double)((a.d1 + 31) / 32 * 32) * (double)((a.d2 + 63) / 64 * 64) * (double)a.d0;
-  const int t = es / 8, b = box ? 1 : 0;
-  const double rows = box && R >= 3 ? c.time : 4.0 + grids * (double)c.waves * width * rows_ns[t][b][R] * 1e-3;
-  return rows < 0.95 * (ring_us[t][b][R] + grids * tiles * ring_ps[t][b][R] * 1e-6);
+  if (a.kinds > 1 && 2048.0 / a.share * (double)c.waves * width < 30000.0) return true;
+  // near each other the fit of FP64 order-2 boxes favours the rows (24^3 x 256 81 / 95)
+  const double near = box && R == 2 && es == 8 ? 0.9 : 1.0;
+  return rows3d_many_us(a, c, R, box, es) < near * ring3d_many_us(ring_load(a, R), R, box, es);
+}
+
+// A grid alone of up to 32 MB, us a step, ring / rows: on the rows, except where their
+// cache reads cost more than the ring's depth.  Stars and 27-point boxes whose planes
+// are a multiple of 1 MB, whose rows then meet in the same cache sets (FP32, 16 and
+// 28 x 512 x 512: star r = 1 9.7 / 12.3, 13.5 / 17.5, r = 4 22 / 30, 31 / 46, box 12.6 / 14.0, 17 / 19; 12 x 600 x
+// 600, r = 2 17.6 / 17.8).  FP32 of order 1 by the fitted times (periodic, whose strips
+// overlap: 64 x 256 x 256 10.1 / 12.6, 160^3 10.8 / 10.2).  FP32 stars of order 3 and 4 on planes of
+// more than 300000 points (12 x 600 x 600 22 / 28; 32 x 384 x 384 26.5 / 26.8), FP64 ones of order 4 of more
+// than 80000 (20 x 300 x 300 23.6 / 26.2; 8 x 400 x 400 20.4 / 18.9).
+inline bool rows3d_better_small(const KArgs& a, const Rows3DCut& c, int R, bool box, int es) {
+  if (box && R >= 2) return true;
+  const int64_t plane = a.d1 * a.d2;
+  if (plane * es % (1 << 20) == 0) return false;
+  if (es == 4 && R == 1) {
+    const int64_t tiles = (int64_t)a.tiles0 * a.tiles1;
+    double chunk = a.chunk, items = (double)chunk3d_items(a);
+    if (items < 256.0) {  // one per CU, as balanced_items3d cuts a grid alone
+      chunk = std::min(chunk, std::max(1.0, std::ceil((double)(a.d0 * tiles) / 256.0)));
+      items = (double)tiles * std::ceil((double)a.d0 / chunk);
+    }
+    const double planes = items * (chunk + 2.0) * 1e-3, points = (double)c.waves * c.NC * c.J * 1e-3;
+    const double rows = box ? 4.7 + 0.084 * points : 4.35 + 0.068 * points;
+    const double ring = box ? 2.6 + 1.69 * planes + 0.9 * (chunk + 2.0) : 2.8 + 1.30 * planes + 0.556 * (chunk + 2.0);
+    return ring > 0.9 * rows;
+  }
+  if (es == 4 && R >= 3) return plane < 300000;
+  return !(es == 8 && R == 4 && a.d0 >= 16 && plane >= 80000);
 }
 
 // Whether the cut beats the plane ring: on ragged or misaligned grids always (the
@@ -406,9 +471,9 @@ inline bool rows3d_better_many(const KArgs& a, const Rows3DCut& c, int R, bool b
 template <typename T, int R, bool BOX>
 inline bool rows3d_better(const KArgs& a, const Rows3DCut& c) {
   if (!dma3d_ok<T>(a)) return true;
-  if (a.share > 0) return rows3d_better_many(a, c, R, BOX, (int)sizeof(T));
+  if (a.share > 0 && (a.share < 2048 || a.kinds > 1)) return rows3d_better_many(a, c, R, BOX, (int)sizeof(T));
   const double pts = (double)a.d0 * (double)a.d1 * (double)a.d2;
-  if (pts * sizeof(T) <= 32e6) return true;
+  if (pts * sizeof(T) <= 32e6) return rows3d_better_small(a, c, R, BOX, (int)sizeof(T));
   constexpr double ring_ps[2][2][5] = {{{0, 0, 4.9, 25.4, 48.3}, {0, 0, 9.7, 27.2, 82.5}},
                                        {{0, 0, 3.6, 16.2, 34.6}, {0, 0, 7.2, 20.8, 66.6}}};
   return BOX && R >= 2 && c.time < pts * ring_ps[pts < 3e7 ? 0 : 1][sizeof(T) / 8][R] * 1e-6;
