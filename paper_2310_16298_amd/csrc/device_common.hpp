@@ -225,20 +225,29 @@ __device__ __forceinline__ S uniform_load(const S* p) {
 
 // Batched launch: a persistent loop over work items blockIdx.x,
 // blockIdx.x + gridDim.x, ... of all grids in the table (every workgroup ends
-// after the last item); each item finds its grid over `first`, 64 entries at a
-// time (a load per round, where a binary search waits for one per halving: six
-// of them were half of a small item's time), and runs item(args, id) with the
-// grid's args in scalar registers.
-template <class F>
+// after the last item); each item finds its grid over `first` and runs
+// item(args, id) with the grid's args in scalar registers.  The search reads 64
+// entries at a time (a load per round, where halving waits for one per step: six
+// of them were half of a small item's time); HALVING: one at a time, in scalar
+// registers only, for kernels of long items whose registers the lanes' search
+// unsettles.
+template <bool HALVING = false, class F>
 __device__ __forceinline__ void for_each_batch_item(const BatchArgs& b, F item) {
   for (int it = blockIdx.x; it < b.total; it += gridDim.x) {
     int lo = 0, n = b.ngrids;  // the last grid with first <= it is in lo .. lo + n - 1
     while (n > 1) {
-      const int step = (n + 63) >> 6, at = (int)(threadIdx.x & 63) * step;
-      const bool le = at < n && b.table[lo + (at < n ? at : 0)].first <= it;  // lane 0: always
-      const int skip = (__builtin_popcountll(__builtin_amdgcn_ballot_w64(le)) - 1) * step;
-      lo += skip;
-      n = n - skip < step ? n - skip : step;
+      if constexpr (HALVING) {
+        const int half = n >> 1;
+        const bool upper = __builtin_amdgcn_readfirstlane(b.table[lo + half].first) <= it;
+        lo = upper ? lo + half : lo;
+        n = upper ? n - half : half;
+      } else {
+        const int step = (n + 63) >> 6, at = (int)(threadIdx.x & 63) * step;
+        const bool le = at < n && b.table[lo + (at < n ? at : 0)].first <= it;  // lane 0: always
+        const int skip = (__builtin_popcountll(__builtin_amdgcn_ballot_w64(le)) - 1) * step;
+        lo += skip;
+        n = n - skip < step ? n - skip : step;
+      }
     }
     const BatchGrid e = uniform_load(&b.table[lo]);
     if (b.launch >= e.limit) continue;  // this grid has done its steps

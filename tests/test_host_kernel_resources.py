@@ -14,7 +14,7 @@ LLVM = os.path.join(os.path.dirname(hipbuild.HIPCC), "..", "llvm", "bin")
 
 @pytest.fixture(scope="module")
 def registers(tmp_path_factory):
-    """Mangled kernel name -> vector registers (accumulation registers included)."""
+    """Mangled kernel name -> vector registers (accumulation registers included), spilled scalar ones."""
     st.load_library()
     tmp = tmp_path_factory.mktemp("kernels")
     fat = str(tmp / "fat")
@@ -33,8 +33,9 @@ def registers(tmp_path_factory):
             continue
         notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", obj], capture_output=True, text=True,
                                check=True).stdout
-        for m in re.finditer(r"\.symbol:\s+'?([^\s']+)\.kd.*?\.vgpr_count:\s+(\d+)", notes, re.S):
-            regs[m.group(1)] = int(m.group(2))
+        for m in re.finditer(r"\.sgpr_spill_count:\s+(\d+)\s+\.symbol:\s+'?([^\s']+)\.kd.*?\.vgpr_count:\s+(\d+)",
+                             notes, re.S):
+            regs[m.group(2)] = (int(m.group(3)), int(m.group(1)))
     assert len(regs) > 500
     return regs
 
@@ -48,18 +49,24 @@ def _of(registers, *parts):
 def test_batched_fp64_order1_outer_products_run_two_waves(registers):
     # 512 vector registers per SIMD lane
     for name, v in _of(registers, "mfma2d_batchIdLi1E").items():
-        assert v <= 256, (name, v)
+        assert v[0] <= 256, (name, v)
 
 
 def test_two_step_stream_of_order_3_runs_two_waves(registers):
     for name, v in _of(registers, "tb3d_stream_kernelIfLi3E").items():
-        assert v <= 256, (name, v)
+        assert v[0] <= 256, (name, v)
     for name, v in _of(registers, "tb3d_stream_kernelIfLi4E").items():
-        assert v <= 300, (name, v)  # one wave; vector weights took 327
+        assert v[0] <= 300, (name, v)  # one wave; vector weights took 327
 
 
 def test_batched_two_step_stream_fits_its_workgroups(registers):
     # 5 and 6 waves a workgroup: a CU takes one less past 128 registers
     for part in ("IfLi2ELb0E", "IfLi1ELb1E"):
         for name, v in _of(registers, "tb3d_stream_batch" + part).items():
-            assert v <= 128, (name, v)
+            assert v[0] <= 128, (name, v)
+
+
+def test_batched_ring_of_fp64_order_4_boxes_keeps_its_scalars(registers):
+    # 57 with a search that stays in scalar registers, 429 with one across the lanes
+    for name, v in _of(registers, "gather3d_batchIdLi4ELb1ELb1E").items():
+        assert v[1] <= 100, (name, v)
