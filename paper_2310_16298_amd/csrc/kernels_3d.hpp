@@ -414,7 +414,8 @@ __global__ __launch_bounds__(kThreads) void gather3d_kernel(KArgs a) {
 
 template <typename T, int R, bool BOX, bool DMA>
 __global__ __launch_bounds__(kThreads) void gather3d_batch(BatchArgs b) {
-  for_each_batch_item<true>(b, [&](const KArgs& x, int id) { gather3d_item<T, R, BOX, DMA, (R < 4)>(x, id); });
+  for_each_batch_item<(sizeof(T) == 8 && BOX && R == 4)>(
+      b, [&](const KArgs& x, int id) { gather3d_item<T, R, BOX, DMA, (R < 4)>(x, id); });
 }
 
 // ---------------------------------------------------------------------------
