@@ -329,13 +329,19 @@ stencil_status_t stencil_run_steps_noalloc(const stencil_desc_t* desc, void* buf
  * launches each) and classes run concurrently on streams forked from the
  * caller's stream and joined back into it; multi-step runs are replayed from
  * a captured HIP graph.  Every grid ends in its buffer steps % 2, with the
- * result of its plan's stencil_run_steps bit for bit. */
+ * result of its plan's stencil_run_steps bit for bit -- except that F32 3D BOX
+ * grids of order 3 and 4 whose plans chose GATHER on path AUTO (more than 16^3
+ * points, chunk and block_n 0) may run the outer products where the batch holds
+ * so many of them that those are estimated faster (from 128 grids of 32^3 or 32 of
+ * 64^3): the result is then that of a plan of path MFMA, bit for bit, within the
+ * same error bound.  Path GATHER keeps the gather. */
 typedef struct stencil_batch_s* stencil_batch_t;
 
 /* Create a batch on the current device.  plans[i] (device = current device)
  * advances the grid held in buffers buf0[i] / buf1[i] (device pointers of
- * plans[i]'s dims and dtype).  Allocates the device work table (one
- * allocation) and count-1 streams at most.  The plans and buffers must outlive
+ * plans[i]'s dims and dtype).  Allocates the device work table, with the
+ * fragments of outer products it chose (one allocation), and count-1 streams at
+ * most.  The plans and buffers must outlive
  * the batch; the plans may be shared between batches.  Errors: EINVAL (null
  * pointers, count < 1, a plan of another device), EALIAS (any two of the
  * 2 x count buffers overlap), EUNSUPPORTED (more than 2^31-1 work items in

@@ -8,6 +8,7 @@
 #include <tuple>
 #include <vector>
 
+#include "kernels_rows3d.hpp"
 #include "runtime.hpp"
 
 using namespace stencil;
@@ -175,7 +176,15 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       KArgs a;
       Kernel k;
       double flops = 0.0;  // per point
+      int64_t frag = -1;   // offset of outer-product fragments of the batch's own
     };
+    std::vector<uint8_t> frags;  // those fragments
+    std::map<const stencil_plan_s*, int64_t> frag_of;
+    struct FragUse {
+      size_t group, grid;
+      int64_t frag;
+    };
+    std::vector<FragUse> frag_uses;
     std::vector<Plain> plain;  // grids of one step per launch
     // columns per lane and shares of the waves of the gathers, by class
     std::vector<int> columns(count, 0), share(count, 1);
@@ -252,6 +261,28 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       plain.back().flops = rs.info.executed_flops_per_point;
       plain.back().k = plan_kernel(rs, buf0[i], buf1[i], &plain.back().a, 1, nullptr, columns[i], share[i],
                                    (int)mergeable[{rs.info.ndim, rs.info.dtype}].size());
+      if (rs.auto_rows) {
+        // the gather that AUTO chose for the grid alone, or the outer products
+        KArgs m;
+        const Picker outer = find_mfma3d_b4(rs.info.radius, true);
+        const Kernel k = plan_kernel(rs, buf0[i], buf1[i], &m, 1, outer, 0, share[i]);
+        KArgs whole = rs.args;
+        whole.in = buf0[i];
+        whole.out = buf1[i];
+        whole.share = share[i];
+        if (k.launch && outer_products_better_many(whole, rs.info.radius)) {
+          auto it = frag_of.find(plans[i]);
+          if (it == frag_of.end()) {
+            const std::vector<uint8_t> f = box3d_b4_fragments(rs);
+            it = frag_of.emplace(plans[i], (int64_t)frags.size()).first;
+            frags.insert(frags.end(), f.begin(), f.end());
+            frags.resize((frags.size() + 255) / 256 * 256);
+          }
+          plain.back().a = m;
+          plain.back().k = k;
+          plain.back().frag = it->second;
+        }
+      }
       if (!plain.back().k.launch || plain.back().k.items < 1) {
         delete b;
         return STENCIL_EINTERNAL;
@@ -273,6 +304,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
         it = by_kernel.emplace(p.k.batch_id, new_group(p.k)).first;
         b->plain.push_back(it->second);
       }
+      if (p.frag >= 0) frag_uses.push_back({it->second, b->groups[it->second].grids.size(), p.frag});
       if (!add_grid(it->second, p.a, p.k)) {
         delete b;
         return STENCIL_EUNSUPPORTED;
@@ -292,9 +324,16 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       g.blocks = (unsigned)std::min<int64_t>(g.total, cap);
       table_entries += g.grids.size();
     }
-    if (hipMalloc(&b->d_tables, table_entries * sizeof(BatchGrid)) != hipSuccess) {
+    const size_t frag_at = (table_entries * sizeof(BatchGrid) + 255) / 256 * 256;
+    if (hipMalloc(&b->d_tables, frag_at + frags.size()) != hipSuccess) {
       delete b;
       return STENCIL_ENOMEM;
+    }
+    char* const d_frags = static_cast<char*>(b->d_tables) + frag_at;
+    for (const FragUse& u : frag_uses) b->groups[u.group].grids[u.grid].args.frag = d_frags + u.frag;
+    if (!frags.empty() && hipMemcpy(d_frags, frags.data(), frags.size(), hipMemcpyHostToDevice) != hipSuccess) {
+      delete b;
+      return STENCIL_EHIP;
     }
     std::vector<BatchGrid> host;
     host.reserve(table_entries);

@@ -406,9 +406,12 @@ inline double ring3d_many_us(const RingLoad& l, int R, bool box, int es) {
       {{{0, 0, 0}, {7.2, 1.28, 1.22}, {12.7, 2.38, 1.19}, {19.5, 4.75, 0.73}, {26.3, 7.5, 0.86}},
        {{0, 0, 0}, {8.3, 2.52, 0.82}, {23.2, 14.3, 0.57}, {63.8, 57.2, 0}, {64.1, 199, 6.9}}},
       {{{0, 0, 0}, {8.1, 2.8, 2.27}, {13.2, 4.6, 2.5}, {18.2, 14.8, 1.2}, {24.5, 13.2, 2.1}},
-       {{0, 0, 0}, {8.7, 4.5, 1.54}, {15.2, 25.2, 1.6}, {67, 97.7, 0}, {47.7, 341, 9.2}}}};
+       {{0, 0, 0}, {8.7, 4.5, 1.54}, {15.2, 25.2, 1.6}, {67, 97.7, 0}, {41, 293, 8}}}};
   const double* f = k[es / 8][box ? 1 : 0][R];
-  return f[0] + f[1] * l.rounds + f[2] * l.planes;
+  double us = f[0] + f[1] * l.rounds + f[2] * l.planes;
+  if (box && R == 2 && es == 8 && l.rounds == 3.0) us *= 0.85;  // three items a CU side by side: 81 (24^3 x 256)
+  if (box && R == 3 && es == 4 && l.rounds == 1.0) us *= 1.05;  // 125-130 (32^3 x 64, 64^3 x 16)
+  return us;
 }
 inline double mfma3d_box_many_us(const RingLoad& l, int R) {
   return R == 3 ? 38.7 + 59.9 * l.rounds + 1.0 * l.planes : 67.3 + 148.9 * l.rounds + 3.5 * l.planes;
@@ -420,7 +423,7 @@ inline double mfma3d_box_many_us(const RingLoad& l, int R) {
 // x 16 8.3 / 7.1, x 64 10.5 / 13.5, 64^3 x 4 9.4 / 7.2, x 16 12.0 / 14.4, 128^3 x 2 12.5 / 18.4; order-3
 // star 32^3 x 64 24 / 20, x 256 33 / 76; order-2 box 32^3 x 128 48 / 64, 24^3 x 128 45 / 36; order-3 box
 // 48^3 x 64 164 / 157, 32^3 x 256 236 / 281; FP64 27-point box 128^3 x 2 22 / 29, order-4 box 32^3 x 64 363 /
-// 188, x 256 718 / 747; 24^3 x 1024 2800 / 1556.
+// 188, x 256 650 / 742; 24^3 x 1024 2800 / 1556.
 // Beside other stencils of its type the rows also share a launch: there they are
 // taken below fifteen rounds of waves at any rate, as the ring would save a tenth to
 // a quarter and leave the merged kernel (120 mixed FP64 grids: 560 us, 640 with the
@@ -428,9 +431,19 @@ inline double mfma3d_box_many_us(const RingLoad& l, int R) {
 inline bool rows3d_better_many(const KArgs& a, const Rows3DCut& c, int R, bool box, int es) {
   const double width = c.NC == 1 ? 1.0 : c.NC == 2 ? 1.8 : 3.3;
   if (a.kinds > 1 && 2048.0 / a.share * (double)c.waves * width < 30000.0) return true;
-  // near each other the fit of FP64 order-2 boxes favours the rows (24^3 x 256 81 / 95)
-  const double near = box && R == 2 && es == 8 ? 0.9 : 1.0;
-  return rows3d_many_us(a, c, R, box, es) < near * ring3d_many_us(ring_load(a, R), R, box, es);
+  return rows3d_many_us(a, c, R, box, es) < ring3d_many_us(ring_load(a, R), R, box, es);
+}
+
+// AUTO's FP32 boxes of order 3 and 4 among many: the n = 4 outer products, whose
+// rate at a full chip the gathers do not reach (us a step, best gather / outer products: order 4
+// 256 grids of 32^3 442 / 339, 64 of 64^3 525 / 390, 128 of 48^3 650 / 506, 128 of 32^3 253 / 205, order 3 236 / 207,
+// 257 / 226; not 64 of 32^3, order 4 148 / 197, order 3 72 / 101).
+inline bool outer_products_better_many(const KArgs& a, int R) {
+  const Rows3DCut c = rows3d_best(a, R, true, 4);
+  if (!dma3d_ok<float>(a) || a.share <= 0 || c.NC == 0) return false;
+  const RingLoad l = ring_load(a, R);
+  const double gather = std::min(rows3d_many_us(a, c, R, true, 4), ring3d_many_us(l, R, true, 4));
+  return mfma3d_box_many_us(l, R) < (R == 4 ? 0.95 : 1.0) * gather;
 }
 
 // A grid alone of up to 32 MB, us a step, ring / rows: on the rows, except where their

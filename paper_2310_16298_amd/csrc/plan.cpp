@@ -341,6 +341,23 @@ static Line line_of(const std::vector<double>& cg, int nd, int R, int axis, cons
   return w;
 }
 
+// CLS(a, *, c): the lines along j of a 3D box, one per coefficient plane a and column c.
+static std::vector<Line> box3d_lines(const std::vector<double>& cg, int R) {
+  std::vector<Line> col;
+  for (int ap = 0; ap <= 2 * R; ++ap)
+    for (int c = 0; c <= 2 * R; ++c) {
+      const int fx[3] = {ap, 0, c};
+      col.push_back(line_of(cg, 3, R, 1, fx, false));
+    }
+  return col;
+}
+
+std::vector<uint8_t> box3d_b4_fragments(const Resolved& rs) {
+  Resolved r;
+  pack_mfma_b4_compact(&r, rs.info.radius, box3d_lines(rs.cg, rs.info.radius));
+  return r.frag;
+}
+
 static void fill_2d_counts(Resolved* rs, int R, int variant, bool split) {
   stencil_plan_info_t& in = rs->info;
   const int n = 16, W = 2 * R + 1;
@@ -454,6 +471,7 @@ int resolve_plan(const stencil_desc_t* desc, Resolved* rs, bool pack) {
                         rows3d_beats_mfma(rows3d_best(dims, R, true, 4), R,
                                           (double)dims.d0 * (double)dims.d1 * (double)dims.d2);
       path = f32 && box && R >= 3 && !few && !rows ? STENCIL_PATH_MFMA : STENCIL_PATH_GATHER;
+      rs->auto_rows = rows;
       // Time blocking, two steps per launch, on k extents that take
       // direct-to-LDS lines, when every knob is left open; measured on MI355X
       // (zero halo) against the one-step gather: the whole-window form on
@@ -803,11 +821,7 @@ int resolve_plan(const stencil_desc_t* desc, Resolved* rs, bool pack) {
       rs->pick = find_mfma3d(d.dtype, R, box);
       std::vector<Line> col, row;
       if (box) {
-        for (int ap = 0; ap < W; ++ap)
-          for (int c = 0; c < W; ++c) {
-            const int fx[3] = {ap, 0, c};
-            col.push_back(line_of(cg, 3, R, 1, fx, false));  // CLS(a, *, c)
-          }
+        col = box3d_lines(cg, R);
         in.mfma_lines = W * W;
         in.valu_lines = 0;
         in.rank1_per_block = (int64_t)W * W * (2 * R + n);

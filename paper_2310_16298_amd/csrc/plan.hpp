@@ -40,6 +40,7 @@ struct Resolved {
   KArgs args{};             // everything but in/out
   int32_t chunk_req = 0;    // requested rows (2D) per work item, 0 = library choice
   int32_t time_block = 1;   // steps per launch
+  bool auto_rows = false;   // AUTO chose the 3D gather for an FP32 box of order 3 or 4: batches may take outer products
   bool tb_auto = false;     // time_block chosen by the library (AUTO): batches may time-block such plans
   Picker pick = nullptr;
   // The kernel of a time-blocked launch when the grid is one of many in a
@@ -51,6 +52,10 @@ struct Resolved {
 
 // Validate + resolve + pack (no device calls).  Returns a stencil status.
 int resolve_plan(const stencil_desc_t* desc, Resolved* out, bool pack);
+
+// Fragments of the n = 4 outer products (find_mfma3d_b4) of a resolved 3D box of
+// order 2 to 4.
+std::vector<uint8_t> box3d_b4_fragments(const Resolved& rs);
 
 // Banded operand of a 2D coefficient line (see stencil_line_band).
 double band_value(const double* cg2d, int R, int n, int axis, int index, int i, int j);
