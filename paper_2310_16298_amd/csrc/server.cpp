@@ -107,6 +107,9 @@ struct Slot {  // pinned staging for the operand upload of one request
   hipEvent_t ready = nullptr;  // last copy from this slot
 };
 
+constexpr double kLaunchSeconds = 4.0e-6, kTickSeconds = 100.0e-6;  // of one launch; of a tick, at least
+constexpr double kMergePart = 0.5;  // of a tick's time: the most that a kernel's requests take and still merge
+
 constexpr size_t kSlotBytes = 64 * 1024;
 constexpr int kSlots = 64;
 
@@ -246,12 +249,26 @@ stencil_status_t rebuild_tables(stencil_server_s* s) {
   s->groups.clear();
   std::map<const void*, size_t> by_kernel;
   std::vector<std::vector<Request*>> members;
-  // requests by kernel, or by the kernel several of theirs merge into
+  // requests by kernel, or by the kernel several of theirs merge into.  A group
+  // takes one step per launch, so a kernel whose requests fill a good part of a
+  // tick's time by themselves stays out: the others of the merged launch would
+  // advance at its pace (a 64^2 star of 100 steps beside a 4096^2 order-3 box: 5.1 ms in
+  // its launches, 0.84 out of them; burst of 16 mixed requests 3.36 / 3.36 ms).
+  std::map<const void*, double> kernel_cost;
+  double tick_cost = kTickSeconds;
+  for (const Request* r : s->active) {
+    double& c = kernel_cost.emplace(r->kernel.batch_id, kLaunchSeconds).first->second;
+    c += r->step_cost;
+    tick_cost = std::max(tick_cost, c);
+  }
+  auto merges = [&](const Request* r) {
+    return r->kernel.merged_id && kernel_cost[r->kernel.batch_id] <= tick_cost * kMergePart;
+  };
   std::map<const void*, std::set<const void*>> kinds;
   for (Request* r : s->active)
-    if (r->kernel.merged_id) kinds[r->kernel.merged_id].insert(r->kernel.batch_id);
+    if (merges(r)) kinds[r->kernel.merged_id].insert(r->kernel.batch_id);
   for (Request* r : s->active) {
-    const bool merged = r->kernel.merged_id && kinds[r->kernel.merged_id].size() > 1;
+    const bool merged = merges(r) && kinds[r->kernel.merged_id].size() > 1;
     const void* id = merged ? r->kernel.merged_id : r->kernel.batch_id;
     auto it = by_kernel.find(id);
     if (it == by_kernel.end()) {
@@ -291,10 +308,10 @@ stencil_status_t rebuild_tables(stencil_server_s* s) {
   if (hipEventSynchronize(s->table_free[k]) != hipSuccess) return STENCIL_EHIP;
   // launches per group: the costliest group does one step per tick (at least
   // 100 us of estimated work), cheaper groups up to 64
-  std::vector<double> cost(s->groups.size(), 4.0e-6);
+  std::vector<double> cost(s->groups.size(), kLaunchSeconds);
   for (size_t g = 0; g < s->groups.size(); ++g)
     for (Request* r : members[g]) cost[g] += r->step_cost;
-  double tau = 100.0e-6;
+  double tau = kTickSeconds;
   for (double c : cost) tau = std::max(tau, c);
   BatchGrid* h = s->h_tables[k];
   int32_t e = 0;
