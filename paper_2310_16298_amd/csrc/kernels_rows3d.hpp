@@ -351,15 +351,16 @@ inline Rows3DCut rows3d_cut(const KArgs& a, int R, bool box, int es, int NC, int
 }
 
 // The best shape for a grid, NC = 0 when the kernel's 32-bit indices do not reach.
-// Alone, and for boxes from order 3 among so many that the chip runs several
-// rounds of their waves: the shortest estimate (four 128^3 grids, one column per
-// lane or the ring / this, us a step: FP32 order-3 and -4 boxes 162 / 113, 315 / 224, FP64
-// 262 / 144, 433 / 273).  Else one of several: one lane column up to 200 columns, as
+// Alone, and for boxes from order 3 that make up most of a launch or are among so
+// many that the chip runs several rounds of their waves: the shortest estimate
+// (four 128^3 grids, one column per lane or the ring / this, us a step: FP32 order-3
+// and -4 boxes 162 / 113, 315 / 224, FP64 262 / 144, 433 / 273; one, order 4 111 / 57).  Else one of several: one lane column up to 200 columns, as
 // each shape more is a launch more.
 inline Rows3DCut rows3d_best(const KArgs& a, int R, bool box, int es) {
   Rows3DCut best;
   if (a.d1 * a.d2 >= (int64_t(1) << 31)) return best;
-  const bool full = a.share > 0 && box && R >= 3 && rows3d_cut(a, R, box, es, 1, 4).waves >= 8 * a.share;
+  const bool full =
+      box && R >= 3 && (a.share > 1024 || (a.share > 0 && rows3d_cut(a, R, box, es, 1, 4).waves >= 8 * a.share));
   for (int k = 0; k < 4; ++k) {
     const int NC = k < 2 ? 1 : k == 2 ? 2 : 4;
     if (NC > a.d2) continue;
