@@ -8,15 +8,12 @@ namespace stencil {
 
 template <int R, bool BOX>
 static Kernel pick_gather3d(KArgs& a, int32_t chunk) {
-  // Small grids among so many that a workgroup each fills the chip.  Fewer are
-  // bound by their latency: a 16^3 FP64 order-2 box takes 42 us a step as one
-  // workgroup, 5 on register rows.
-  if (a.share > 0 && a.share <= 8) {
-    const Kernel whole = whole3d_kernel<double, R, BOX>(a, chunk);
-    if (whole.launch) return whole;
-  }
   if (chunk == 0) {
     const Rows3DCut c = rows3d_best(a, R, BOX, (int)sizeof(double));
+    if (a.share > 0 && whole3d_better(a, c, R, BOX, (int)sizeof(double))) {
+      const Kernel whole = whole3d_kernel<double, R, BOX>(a, chunk);
+      if (whole.launch) return whole;
+    }
     if (c.NC && rows3d_better<double, R, BOX>(a, c)) return rows3d_kernel_for<double, R, BOX>(a, c);
   }
   if (dma3d_ok<double>(a)) return kernel3d<gather3d_kernel<double, R, BOX, true>, gather3d_batch<double, R, BOX, true>>(a, R, chunk);

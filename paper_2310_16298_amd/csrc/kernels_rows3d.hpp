@@ -401,6 +401,16 @@ inline double rows3d_many_us(const KArgs& a, const Rows3DCut& c, int R, bool box
   return f[0] + f[1] * (2048.0 / a.share) * (double)c.waves * width * 1e-3;
 }
 
+// The same on the whole-grid gather, a workgroup a grid: 1 to 256 grids take one
+// round, whose time follows the grid's points (fitted to 32 .. 300 grids of 8^3 .. 20^3).
+inline double whole3d_many_us(double points, int R, bool box, int es) {
+  constexpr double k[2][2][5][2] = {
+      {{{0, 0}, {4.2, 2.56}, {4.9, 3.36}, {5.8, 4.16}, {7.2, 4.97}}, {{0, 0}, {4.1, 3.30}, {5.4, 7.70}, {8.2, 16.9}, {12.3, 33.0}}},
+      {{{0, 0}, {4.2, 2.76}, {5.2, 3.46}, {5.9, 4.36}, {7.1, 5.55}}, {{0, 0}, {4.2, 3.64}, {7.0, 9.31}, {8.4, 28.6}, {13.1, 57.7}}}};
+  const double* f = k[es / 8][box ? 1 : 0][R];
+  return f[0] + f[1] * points * 1e-3;
+}
+
 // The same on the plane ring and on the FP32 outer products of order 3 and 4.
 inline double ring3d_many_us(const RingLoad& l, int R, bool box, int es) {
   constexpr double k[2][2][5][3] = {
@@ -491,6 +501,20 @@ inline bool rows3d_better(const KArgs& a, const Rows3DCut& c) {
   constexpr double ring_ps[2][2][5] = {{{0, 0, 4.9, 25.4, 48.3}, {0, 0, 9.7, 27.2, 82.5}},
                                        {{0, 0, 3.6, 16.2, 34.6}, {0, 0, 7.2, 20.8, 66.6}}};
   return BOX && R >= 2 && c.time < pts * ring_ps[pts < 3e7 ? 0 : 1][sizeof(T) / 8][R] * 1e-6;
+}
+
+// Whether one of many small grids, a workgroup each, beats the cut.  From 228 on
+// they fill the chip.  Fewer are bound by a workgroup's latency, so the rows have
+// them while they end sooner (us a step, whole / rows: 8^3 FP64 order-4 box, 64 grids
+// 42 / 21, 200 43 / 54; 27-point box 128 grids 5.9 / 5.3, 200 5.9 / 7.2; 12^3 FP64
+// order-3 star 64 grids 12.7 / 7.5, 150 12.8 / 15.2; 16^3 order-3 star, 128 grids
+// 22 / 19, 200 22 / 28; order-4 box 32 grids 250 / 30).  Beside other stencils the
+// rows share a launch.
+inline bool whole3d_better(const KArgs& a, const Rows3DCut& c, int R, bool box, int es) {
+  if (a.share <= 8 || !c.NC) return a.share <= 8;
+  if (a.kinds > 1) return false;
+  const double points = (double)a.d0 * (double)a.d1 * (double)a.d2;
+  return whole3d_many_us(points, R, box, es) < rows3d_many_us(a, c, R, box, es);
 }
 
 // AUTO's choice between the cut and the n = 4 outer products for FP32 boxes of

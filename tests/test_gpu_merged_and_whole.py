@@ -80,3 +80,29 @@ def test_many_small_grids_whole(dtype, r, shape, bc):
         batch.close()
         plan.close()
         ring.close()
+
+
+# Below 228 grids the faster by the fitted times: a workgroup a grid takes one round
+# however many they are, the rows' time follows their number.
+@pytest.mark.parametrize("n,count,r,shape,dtype,kernel", [
+    (8, 64, 1, st.BOX, st.F64, "rows3d_batch"), (8, 200, 1, st.BOX, st.F64, "gather3d_whole_batch"),
+    (8, 64, 4, st.BOX, st.F64, "rows3d_batch"), (8, 200, 2, st.STAR, st.F32, "gather3d_whole_batch"),
+    (12, 64, 3, st.STAR, st.F64, "rows3d_batch"), (12, 150, 3, st.STAR, st.F64, "gather3d_whole_batch"),
+    (16, 64, 3, st.STAR, st.F64, "rows3d_batch"), (16, 200, 3, st.STAR, st.F64, "gather3d_whole_batch"),
+    (16, 200, 4, st.BOX, st.F64, "rows3d_batch"), (16, 200, 3, st.BOX, st.F32, "rows3d_batch"),
+])
+def test_whole_grids_below_a_full_chip(n, count, r, shape, dtype, kernel):
+    torch = torch_cuda()
+    plan = _plan((n, n, n), r, shape, P, dtype)
+    x = _grid(torch, (n, n, n), 830, dtype)
+    want = plan.run_steps(x.clone(), torch.empty_like(x), 3)
+    b0 = x.repeat(count, 1, 1, 1)
+    b1 = torch.full_like(b0, float("nan"))
+    batch = st.Batch([plan] * count, list(b0), list(b1))
+    names = launched(torch, lambda: batch.run_steps(1))
+    assert len(names) == 1 and kernel in names[0], names
+    b0.copy_(x.expand_as(b0))
+    out = (b0, b1)[batch.run_steps(3)]
+    torch.cuda.synchronize()
+    assert torch.equal(out, want.expand_as(out))
+    batch.close()
