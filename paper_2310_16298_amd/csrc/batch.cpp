@@ -231,7 +231,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
         bool ok = true;
         for (int sz = 1; sz <= T && ok; ++sz) {
           ks[sz] = plan_kernel(rs, buf0[i], buf1[i], &as[sz], sz, rs.pick_batch, columns[i], share[i]);
-          ok = ks[sz].launch && ks[sz].items >= 1;
+          ok = ks[sz].launch_batch && ks[sz].items >= 1;
         }
         if (ok) {
           auto cit = by_class.find({ks[T].batch_id, T});
@@ -270,7 +270,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
         whole.in = buf0[i];
         whole.out = buf1[i];
         whole.share = share[i];
-        if (k.launch && outer_products_better_many(whole, rs.info.radius)) {
+        if (k.launch_batch && outer_products_better_many(whole, rs.info.radius)) {
           auto it = frag_of.find(plans[i]);
           if (it == frag_of.end()) {
             const std::vector<uint8_t> f = box3d_b4_fragments(rs);
@@ -283,7 +283,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
           plain.back().frag = it->second;
         }
       }
-      if (!plain.back().k.launch || plain.back().k.items < 1) {
+      if (!plain.back().k.launch_batch || plain.back().k.items < 1) {
         delete b;
         return STENCIL_EINTERNAL;
       }

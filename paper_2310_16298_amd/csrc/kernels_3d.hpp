@@ -504,33 +504,25 @@ __device__ __forceinline__ void gather3d_whole_item(const KArgs& a) {
 }
 
 template <typename T, int R, bool BOX, int VOL>
-__global__ __launch_bounds__(kThreads) void gather3d_whole_kernel(KArgs a) {
-  gather3d_whole_item<T, R, BOX, VOL>(a);
-}
-
-template <typename T, int R, bool BOX, int VOL>
 __global__ __launch_bounds__(kThreads) void gather3d_whole_batch(BatchArgs b) {
   for_each_batch_item(b, [&](const KArgs& x, int) { gather3d_whole_item<T, R, BOX, VOL>(x); });
 }
 
 // The whole-grid kernel for a grid that fits 16, 32, 64 or 128 KiB of LDS
-// with its halo (the smallest: more workgroups per CU) and leaves the chunk
-// to the library, else none.
+// with its halo (the smallest: more workgroups per CU), else none.
 template <typename T, int R, bool BOX>
-inline Kernel whole3d_kernel(const KArgs& a, int32_t chunk) {
+inline Kernel whole3d_kernel(const KArgs& a) {
   constexpr int SMALL = 16384 / (int)sizeof(T), MEDIUM = 32768 / (int)sizeof(T), LARGE = 65536 / (int)sizeof(T),
                 HUGE = 131072 / (int)sizeof(T);
-  if (chunk != 0) return Kernel{};
   if (whole3d_fits<T, SMALL>(a.d0, a.d1, a.d2, R))
-    return kernel_of<gather3d_whole_kernel<T, R, BOX, SMALL>, gather3d_whole_batch<T, R, BOX, SMALL>>(1);
+    return batch_kernel_of<gather3d_whole_batch<T, R, BOX, SMALL>>(1);
   if (whole3d_fits<T, MEDIUM>(a.d0, a.d1, a.d2, R))
-    return kernel_of<gather3d_whole_kernel<T, R, BOX, MEDIUM>, gather3d_whole_batch<T, R, BOX, MEDIUM>>(1);
+    return batch_kernel_of<gather3d_whole_batch<T, R, BOX, MEDIUM>>(1);
   if (whole3d_fits<T, LARGE>(a.d0, a.d1, a.d2, R))
-    return kernel_of<gather3d_whole_kernel<T, R, BOX, LARGE>, gather3d_whole_batch<T, R, BOX, LARGE>>(1);
-  // 128 KiB (one workgroup per CU) only for grids of at most 16^3 points:
-  // larger ones keep the tiled kernel's parallelism when launched alone
+    return batch_kernel_of<gather3d_whole_batch<T, R, BOX, LARGE>>(1);
+  // 128 KiB (one workgroup per CU) only for grids of at most 16^3 points
   if (a.d0 * a.d1 * a.d2 <= 4096 && whole3d_fits<T, HUGE>(a.d0, a.d1, a.d2, R))
-    return kernel_of<gather3d_whole_kernel<T, R, BOX, HUGE>, gather3d_whole_batch<T, R, BOX, HUGE>>(1);
+    return batch_kernel_of<gather3d_whole_batch<T, R, BOX, HUGE>>(1);
   return Kernel{};
 }
 

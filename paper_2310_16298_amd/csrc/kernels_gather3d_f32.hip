@@ -11,8 +11,8 @@ static Kernel pick_gather3d(KArgs& a, int32_t chunk) {
   if (chunk == 0) {
     const Rows3DCut c = rows3d_best(a, R, BOX, (int)sizeof(float));
     if (a.share > 0 && whole3d_better(a, c, R, BOX, (int)sizeof(float))) {
-      const Kernel whole = whole3d_kernel<float, R, BOX>(a, chunk);
-      if (whole.launch) return whole;
+      const Kernel whole = whole3d_kernel<float, R, BOX>(a);
+      if (whole.launch_batch) return whole;
     }
     if (c.NC && rows3d_better<float, R, BOX>(a, c)) return rows3d_kernel_for<float, R, BOX>(a, c);
   }

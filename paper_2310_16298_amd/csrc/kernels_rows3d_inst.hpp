@@ -8,7 +8,11 @@ namespace stencil {
 template <typename T, bool BOX, int R, int NC, bool TALL>
 static Kernel rows3d_shape(int64_t items) {
   constexpr int J = rows3d_j((int)sizeof(T), R, NC, TALL);
-  return kernel_of<rows3d_kernel<T, R, BOX, NC, J>, rows3d_batch<T, R, BOX, NC, J>>(items);
+  // the cuts that a grid of a batch takes
+  if constexpr (J == 4 ? NC != 2 || (BOX && R >= 3) : NC != 1)
+    return kernel_of<rows3d_kernel<T, R, BOX, NC, J>, rows3d_batch<T, R, BOX, NC, J>>(items);
+  else
+    return kernel_of<rows3d_kernel<T, R, BOX, NC, J>>(items);
 }
 
 template <typename T, bool BOX, int R>

@@ -89,4 +89,14 @@ inline Kernel kernel_of(int64_t items) {
   return k;
 }
 
+// A kernel that only batched launches take.
+template <auto KB>
+inline Kernel batch_kernel_of(int64_t items) {
+  Kernel k;
+  k.launch_batch = launch_batched<KB, 256>;
+  k.batch_id = reinterpret_cast<const void*>(KB);
+  k.items = items;
+  return k;
+}
+
 }  // namespace stencil
