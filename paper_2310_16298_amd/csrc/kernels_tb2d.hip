@@ -98,6 +98,19 @@ static bool lds_tiles_better(const KArgs& a) {
   }
 }
 
+// Ragged extents or misaligned buffers: the FP64 order-4 box, whose walk is slowest to
+// fill, on tiles staged by element.  us a step at two steps a launch, tiles / walk,
+// zero halo: 64 x 66 4.7 / 6.1, 300 x 201 4.8 / 9.4, 17 x 5001 4.7 / 10.0, 1021 x 1531
+// 13.5 / 15.8, 2001 x 2003 31 / 35, 3001 x 3003 65 / 59, 40000 x 5 18.0 / 17.3; periodic: 64 x 66 7.4 /
+// 6.2, 300 x 65 7.1 / 6.2, 300 x 201 6.6 / 9.4, 3000 x 9 6.6 / 9.4, 901 x 777 10.5 / 12.7, 1021 x 1531
+// 15.7 / 15.6, 40000 x 5 27 / 17.
+template <typename T, int R, bool BOX>
+static bool any_tiles_better(const KArgs& a) {
+  if (sizeof(T) == 4 || R != 4 || !BOX || a.d1 <= 8) return false;
+  const int64_t pts = a.d0 * a.d1;
+  return a.periodic ? pts >= 25000 && pts < 1500000 : pts < 5000000;
+}
+
 // Among many grids the tiles win where all of the class's grids together are about
 // one round of waves: the walk's chunks are as short as their fill then, and
 // there are too few of them to hide it (us a step, tiles / walk, zero halo: 16 FP32 grids
@@ -126,8 +139,9 @@ static Kernel pick_tb2d(KArgs& a, int32_t chunk) {
   // a launch of one step (the remainder of a run): the one-step gather
   if (a.steps <= 1) return find_gather2d(std::is_same<T, double>::value ? STENCIL_F64 : STENCIL_F32, R, BOX)(a, chunk);
   if constexpr (tb2d_dma_built<T>(R, BOX)) {
-    if (tb2d_fast<T>(a) && a.zeros != nullptr &&
-        (MANY ? lds_tiles_better_many<T, R, BOX>(a) : lds_tiles_better<T, R, BOX>(a))) {
+    const bool fast = tb2d_fast<T>(a) && a.zeros != nullptr;
+    if (fast ? (MANY ? lds_tiles_better_many<T, R, BOX>(a) : lds_tiles_better<T, R, BOX>(a))
+             : (!MANY && any_tiles_better<T, R, BOX>(a))) {
       int TM = TbDmaShape<T, R, 2>::TM;
       a.tiles1 = (int32_t)((a.d1 + 63) / 64);
       // FP64 grids of fewer tiles than CUs (launch-bound: 512^2 has 128) take
@@ -136,7 +150,8 @@ static Kernel pick_tb2d(KArgs& a, int32_t chunk) {
           !MANY && !std::is_same<T, float>::value && (int64_t)((a.d0 + TM - 1) / TM) * a.tiles1 < 256;
       if (small) TM = kTbSmallRows;
       a.tiles0 = (int32_t)((a.d0 + TM - 1) / TM);
-      return tb2d_dma<T, BOX>(R, a.steps, (int64_t)a.tiles0 * a.tiles1, small);
+      const int64_t items = (int64_t)a.tiles0 * a.tiles1;
+      return fast ? tb2d_dma<T, BOX>(R, a.steps, items, small) : tb2d_any_box4(items, small);
     }
   }
   const int NC = cut_rs2d<T, R, BOX, MANY>(a);

@@ -3,7 +3,8 @@
 // direct-to-LDS windows (column extent a multiple of 4, 16-byte aligned
 // buffers, a zero line).  The register-streaming kernel (kernels_rs2d.hpp)
 // does the same on every grid and mostly faster; these tiles serve the orders
-// and sizes named at lds_tiles_better (kernels_tb2d.hip).
+// and sizes named at lds_tiles_better (kernels_tb2d.hip).  ANY: other extents and
+// buffers, staged and stored element by element (FP64 boxes of order 4).
 //
 // A workgroup owns a TM x 64 output tile.  It stages the tile's window with a
 // halo of HW = round_up(r TS, 4) on every side into LDS once, applies TS steps
@@ -64,7 +65,7 @@ template <typename T> struct TbVec;
 template <> struct TbVec<float> { typedef floatx4 type; };
 template <> struct TbVec<double> { typedef double __attribute__((ext_vector_type(2))) type; };
 
-template <typename T, int R, bool BOX, int TS, int TM_ = 0>
+template <typename T, int R, bool BOX, int TS, int TM_ = 0, bool ANY = false>
 __device__ __forceinline__ void tb2d_dma_item(const KArgs& a, int item) {
   typedef TbDmaShape<T, R, TS, TM_> S;
   typedef typename TbVec<T>::type V;
@@ -91,9 +92,21 @@ __device__ __forceinline__ void tb2d_dma_item(const KArgs& a, int item) {
     const int inst = k * 4 + w;
     if (inst >= S::NI) break;  // wave-uniform
     const int line = inst * 64 + lane;
-    const T* src = zeros;
+    [[maybe_unused]] const T* src = zeros;
     const int row = line / S::LPR, lc = line - (line / S::LPR) * S::LPR;
-    if (row < S::WM && lc >= S::MARGIN && lc < S::LPR - S::MARGIN) {
+    const bool inside = row < S::WM && lc >= S::MARGIN && lc < S::LPR - S::MARGIN;
+    if constexpr (ANY) {
+      V t4;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        t4[e] = T(0);
+        const int64_t g = map_index(i0 + row, M, periodic), cc = map_index(j0 - 4 + VEC * lc + e, N, periodic);
+        if (inside && g >= 0 && cc >= 0) t4[e] = in[g * N + cc];
+      }
+      *reinterpret_cast<V*>(buf + line * VEC) = t4;
+      continue;
+    }
+    if (inside) {
       const int64_t g = map_index(i0 + row, M, periodic);
       const int64_t cc = map_index(j0 - 4 + VEC * lc, N, periodic);
       if (g >= 0 && cc >= 0) src = in + g * N + cc;
@@ -187,7 +200,7 @@ __device__ __forceinline__ void tb2d_dma_item(const KArgs& a, int item) {
     __syncthreads();
   }
 
-  // store the tile: window rows HW .., columns HW .. (N % 4 == 0: whole segments)
+  // store the tile: window rows HW .., columns HW .. (whole segments unless ANY)
   constexpr int TSEG = S::TN / 4;
 #pragma unroll
   for (int k = 0; k < (S::TM * TSEG + 255) / 256; ++k) {
@@ -196,15 +209,21 @@ __device__ __forceinline__ void tb2d_dma_item(const KArgs& a, int item) {
     const int64_t gi = (int64_t)ti * S::TM + x, gj = (int64_t)tj * S::TN + 4 * sg;
     if (gi >= M || gj >= N) continue;
     const V* sv = reinterpret_cast<const V*>(buf + (S::HW + x) * S::P + 4 + S::HW + 4 * sg);
+    if constexpr (ANY) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (gj + e < N) out[gi * N + gj + e] = sv[e / VEC][e % VEC];
+      continue;
+    }
     V* dv = reinterpret_cast<V*>(out + gi * N + gj);
 #pragma unroll
     for (int e = 0; e < 4 / VEC; ++e) dv[e] = sv[e];
   }
 }
 
-template <typename T, int R, bool BOX, int TS, int TM_ = 0>
+template <typename T, int R, bool BOX, int TS, int TM_ = 0, bool ANY = false>
 __global__ __launch_bounds__(256) void tb2d_dma_kernel(KArgs a) {
-  tb2d_dma_item<T, R, BOX, TS, TM_>(a, xcd_remap(blockIdx.x, gridDim.x));
+  tb2d_dma_item<T, R, BOX, TS, TM_, ANY>(a, xcd_remap(blockIdx.x, gridDim.x));
 }
 
 template <typename T, int R, bool BOX, int TS>
@@ -222,5 +241,7 @@ constexpr bool tb2d_dma_built(int R, bool box) {
 }
 template <typename T, bool BOX>
 Kernel tb2d_dma(int R, int steps, int64_t items, bool small_tiles);
+// Two steps of an FP64 order-4 box of any extents and buffers.
+Kernel tb2d_any_box4(int64_t items, bool small_tiles);
 
 }  // namespace stencil

@@ -49,6 +49,11 @@ Kernel tb2d_dma<double, true>(int R, int steps, int64_t items, bool small_tiles)
   return small_tiles ? small<4, true, 2>(items) : tiles<double, 4, true, 2>(items);
 }
 
+Kernel tb2d_any_box4(int64_t items, bool small_tiles) {
+  return small_tiles ? kernel_of<tb2d_dma_kernel<double, 4, true, 2, kTbSmallRows, true>>(items)
+                     : kernel_of<tb2d_dma_kernel<double, 4, true, 2, 0, true>>(items);
+}
+
 template <>
 Kernel tb2d_dma<double, false>(int R, int steps, int64_t items, bool small_tiles) {
   if (R == 2) return order2<false>(steps, items, small_tiles);

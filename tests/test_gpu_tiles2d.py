@@ -94,3 +94,31 @@ def test_tiles_in_a_batch(dims, count, r, shape, dtype, bc):
                 assert torch.equal(out[j], want), (steps, j)
     batch.close()
     plan.close()
+
+
+# staged by element: 16-row and 32-row tiles, every remainder of a segment, buffers one
+# element off a 16-byte line; the cells around the buffers stay as they are
+@pytest.mark.parametrize("bc,dims,shift", [
+    (Z, (1, 9), 0), (Z, (17, 10), 0), (Z, (64, 63), 0), (Z, (66, 65), 1), (Z, (64, 64), 1), (Z, (300, 201), 0),
+    (Z, (1021, 1531), 0), (Z, (17, 5001), 1), (P, (301, 201), 0), (P, (300, 202), 1), (P, (3001, 9), 0),
+    (P, (9, 3001), 0), (P, (901, 777), 0), (P, (300, 204), 1),
+])
+def test_ragged_order4_boxes(bc, dims, shift):
+    torch = torch_cuda()
+    c = inputs.coefficients(2, 4, st.BOX, seed=320, dtype=np.float64)
+    a0 = _grid(dims, 321, st.F64)
+    flat = [torch.full((a0.size + 64 + shift,), 7.5, dtype=torch.float64, device="cuda") for _ in range(2)]
+    x, y = (f[32 + shift:32 + shift + a0.size].view(dims) for f in flat)
+    plan = st.Plan(dims, 4, st.BOX, c, boundary=bc, dtype=st.F64, time_block=2)
+    names = launched(torch, lambda: plan.run_steps(x, y, 2))
+    assert len(names) == 1 and "tb2d_dma_kernel" in names[0], names
+    for steps in (2, 4, 5):
+        x.copy_(torch.from_numpy(a0))
+        y.fill_(float("nan"))
+        got = plan.run_steps(x, y, steps).clone()
+        torch.cuda.synchronize()
+        assert torch.equal(got, _run(torch, a0, 4, st.BOX, c, bc, st.F64, 1, steps)), steps
+    for f in flat:
+        edge = torch.cat([f[:32 + shift], f[32 + shift + a0.size:]])
+        assert bool((edge == 7.5).all())
+    plan.close()
