@@ -84,10 +84,10 @@ typedef enum { STENCIL_F32 = 0, STENCIL_F64 = 1 } stencil_dtype_t;
 
 typedef enum {
   STENCIL_PATH_AUTO = 0,        /* library picks, from measurements on MI355X: MFMA for F32 boxes of
-                                   order >= 3 (2D and 3D; 3D boxes of up to about 256^3 points
+                                   order >= 3 (2D at one step per launch, and 3D; 3D boxes of
+                                   more than 16^3 and up to about 256^3 points
                                    and 3D GENERAL stencils with at most 88 / 128
-                                   nonzero taps at order 3 / 4 take GATHER), F64 3D stars of order
-                                   4 and 2D GENERAL
+                                   nonzero taps at order 3 / 4 take GATHER) and 2D GENERAL
                                    stencils (FP32 grids wider than 64 columns: the line cover or
                                    the nonzero-tap gather, whichever a cost fitted on MI355X
                                    prefers -- 12290 + 403 n per point for n nonzero taps (n capped
@@ -132,10 +132,11 @@ typedef struct {
                            instructions (F64, 2D orthogonal stars, 3D boxes up to order 2); any
                            other resolved block edge: EUNSUPPORTED; ignored by the GATHER path */
   int32_t chunk;        /* output rows (2D) or i-planes (3D) per workgroup work item: 0 = library
-                           choice (in a batch, a grid on the 3D GATHER path that fits the LDS with
-                           its halo, 8^3 or 16^3 say, is then one work item computed whole by
-                           one workgroup); rounded up to the kernel's row block and clipped to the
-                           extent */
+                           choice (in a batch of 228 grids of one order and shape or more, fewer
+                           where that is estimated faster, a grid on the 3D GATHER path that fits
+                           the LDS with its halo, 8^3 or 16^3 say, is then one work item computed
+                           whole by one workgroup); rounded up to the kernel's row block and
+                           clipped to the extent */
   int32_t time_block;   /* steps fused per launch (time blocking; the temporal reuse Section 6
                            leaves to future work): 1 = one step per launch; T > 1: each launch
                            advances T steps on overlapped pieces (halo r*T) held in registers or
@@ -180,7 +181,8 @@ typedef struct {
   int32_t lines;         /* resolved stencil_lines_t */
   int32_t ndim, radius, shape, boundary, dtype;
   int32_t taps;          /* nonzero-capable taps: (2r+1)^d box, 2rd+1 star (Section 3.4) */
-  int32_t tile_rows;     /* output tile of one workgroup: rows (2D) or j-rows (3D) */
+  int32_t tile_rows;     /* output tile of one workgroup: rows (2D) or j-rows (3D); nominal where
+                            the launch picks a kernel without tiles (row walks, register rows) */
   int32_t tile_cols;     /* ... contiguous columns */
   int32_t block_n;       /* edge n of one MFMA output block (4 or 16); 0 for GATHER */
   int32_t mfma_lines;    /* coefficient lines issued on the matrix cores */
@@ -319,10 +321,9 @@ stencil_status_t stencil_run_steps_noalloc(const stencil_desc_t* desc, void* buf
  * CU) x (CUs) workgroups loop over the (grid, tile) work items of all its
  * grids.  Grids whose plans the library time-blocked (stencil_plan_info's
  * time_block T > 1 with the descriptor's time_block 0) advance up to T steps
- * per launch, on kernels picked for a grid among many: 2D FP64 grids keep
- * tiles of full height (32 rows) however small, and 3D grids too small for
- * the streaming form (whose own plans take the whole-window form) run one
- * step per launch.  Grids sharing the T-step kernel form a class, whose run of
+ * per launch, on kernels picked for a grid among many (2D: cut for the grid's
+ * share of a chip's waves; 3D grids too small for the streaming form, whose own
+ * plans take the whole-window form, run one step per launch).  Grids sharing the T-step kernel form a class, whose run of
  * `steps` steps is the fewest launches of at most T steps (as even as
  * possible) whose count has the parity of `steps`, each launch size its own
  * group (one step: the plans' one-step kernel).  Plain groups (steps
@@ -381,7 +382,9 @@ stencil_status_t stencil_batch_destroy(stencil_batch_t batch);
  *      estimate of each group's cost per step (HBM bytes and executed flops
  *      of its plans) so that the costliest group does one step and cheaper
  *      groups up to 64 in about the same time; a request takes part in the
- *      first min(k, steps left) launches of its group;
+ *      first min(k, steps left) launches of its group; one-step gathers of
+ *      several orders and shapes make one group, except those whose own kernel
+ *      would take a good part of the tick;
  *   3. copies each request that has done its steps to its output buffer and
  *      releases its arena block.
  * The arena is one device allocation made at creation, with a first-fit
@@ -390,7 +393,7 @@ stencil_status_t stencil_batch_destroy(stencil_batch_t batch);
  * device) grow when more requests are resident than ever before.  All work
  * runs on the server's own stream (stencil_server_stream), in order.  A
  * request's result equals the result of a plan of the same descriptor run
- * alone (same kernel, same arithmetic).  Not thread-safe: one thread drives a
+ * alone (same arithmetic, whichever kernel of its path the company leads to).  Not thread-safe: one thread drives a
  * server.  Time-blocked descriptors (time_block > 1) are rejected
  * (EUNSUPPORTED); a time block the library chose (time_block 0) is run one
  * step per launch, with the same arithmetic. */

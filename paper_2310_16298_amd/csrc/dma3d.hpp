@@ -20,7 +20,11 @@ namespace stencil {
 // FMAs side by side only if they do not both read a scalar operand (us a step,
 // scalar / vector weights: plane ring 512^3 order-2 box 560 / 481, 384^3 266 / 221,
 // 256^3 order-3 star 37.5 / 32.6; two-step stream 512^3 27-point box 213 / 182, 384^3
-// 96 / 82, order-2 star 171 / 164).  FP64 issues one wave at a time either way.
+// 96 / 82, order-2 star 171 / 164).  Scalar / vector time, by size: the ring
+// alone, box 1 0.94-1.10, box 2 0.94-1.24, box 3 1.36-2.2, stars 0.95-1.15; batched, box 1
+// 0.95-1.18, box 2 1.08-1.54, box 3 1.04-1.52, star 1 1.0-1.15, star 2 0.96-1.32, star 3
+// 1.01-1.29.  VW false where the registers cost more (the kernels' own comments).
+// FP64 issues one wave at a time either way.
 template <typename T, bool VW = true>
 __device__ __forceinline__ T vector_weight(T w) {
   if constexpr (sizeof(T) == 4 && VW) asm("" : "+v"(w));

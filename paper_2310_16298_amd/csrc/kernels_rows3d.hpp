@@ -520,8 +520,8 @@ inline bool whole3d_better(const KArgs& a, const Rows3DCut& c, int R, bool box, 
 // AUTO's choice between the cut and the n = 4 outer products for FP32 boxes of
 // order 3 and 4: those take 97 / 225 us however small the grid, and 14.2 / 25.7 ps a
 // point at 256^3, 11.4 / 20.9 at 320^3, 8.9 / 16.6 at 512^3 (the rows: 10.0 / 20.5 at
-// 256^3, 13.4 / 28.2 at 320^3).  Up to 16^3 the outer products stay, the choice their
-// callers know.
+// 256^3, 13.4 / 28.2 at 320^3).  Up to 16^3 the outer products are the documented path
+// (a plan reports it, and the paths round differently), not the faster one.
 inline bool rows3d_beats_mfma(const Rows3DCut& c, int R, double pts) {
   const double ps = R == 3 ? (pts < 2e7 ? 13.5 : pts < 5e7 ? 11.0 : 8.9) : (pts < 2e7 ? 25.0 : pts < 5e7 ? 20.5 : 16.6);
   return c.NC && pts > 4096 && c.time < std::max(R == 3 ? 97.0 : 225.0, pts * ps * 1e-6);

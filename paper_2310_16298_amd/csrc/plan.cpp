@@ -517,8 +517,9 @@ int resolve_plan(const stencil_desc_t* desc, Resolved* rs, bool pack) {
       // windows; the register-streaming gather does not need them and beats the
       // outer products' register-staged windows by 2-5x (1021 x 1531, one step: FP32
       // stars 14-15 us against 5.5-6.9, boxes r = 3, 4 18-19 against 8.8-11.8, FP64
-      // boxes 17-34 against 6-18; 75^2 17-22 against 3.6-7.5).  Up to 68 columns
-      // such grids keep the outer products, the choice their callers know.
+      // boxes 17-34 against 6-18; 75^2 17-22 against 3.6-7.5).  The line at 68 columns is
+      // not one of speed: the outer products are the documented path of the
+      // grids below it (a plan reports its path, and the paths round differently).
       // FP64 GENERAL ones take the all-tap gather, one step per launch (5413 x 2017,
       // order 4: 191 us a step as a line cover, 55); FP32 ones keep the cover.
       const bool ragged = !dma_cols && d.dims[1] > 68 && !(general && f32) && d.lines == STENCIL_LINES_AUTO && d.block_n == 0 &&
@@ -542,8 +543,8 @@ int resolve_plan(const stencil_desc_t* desc, Resolved* rs, bool pack) {
           d.block_n == 0 && d.chunk == 0 && d.reg_rows == 0 && d.tile_width == 0) {
         int t = kAutoTimeBlock[f32 ? 0 : 1][box ? 1 : 0][R];
         // the FP64 order-3 box: two steps with its weights in registers take 161 us
-        // a step at 8192^2 against 223 alone, 4.5 against 6.3 at 512^2; up to 96
-        // columns it keeps one step, the choice its callers know
+        // a step at 8192^2 against 223 alone, 4.5 against 6.3 at 512^2.  The line at 96
+        // columns is not one of speed: one step is the documented block below it
         if (!f32 && box && R == 3 && d.dims[1] > 96) t = 2;
         if (t > 1) {
           path = STENCIL_PATH_GATHER;
