@@ -188,6 +188,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
     std::vector<Plain> plain;  // grids of one step per launch
     // columns per lane and shares of the waves of the gathers, by class
     std::vector<int> columns(count, 0), share(count, 1);
+    std::vector<double> points(count, 0.0);  // of the grid's class
     std::map<std::pair<Picker, int>, std::vector<int32_t>> members;
     for (int32_t i = 0; i < count; ++i) {
       const Resolved& rs = plans[i]->rs;
@@ -207,6 +208,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       const bool d2 = grids[0]->info.ndim == 2;
       for (int32_t i : m.second)
         share[i] = std::max(1, (int)(2048.0 * (d2 ? (double)plans[i]->grid_bytes / bytes : 1.0 / (double)grids.size())));
+      for (int32_t i : m.second) points[i] = bytes / (grids[0]->info.dtype == STENCIL_F64 ? 8.0 : 4.0);
       if (!d2) continue;
       const int nc = rs2d_batch_cut(grids, share.data(), m.second.data());
       for (int32_t i : m.second) columns[i] = nc;
@@ -218,6 +220,14 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       if ((rs.family == FAM_GATHER2D || rs.family == FAM_GATHER3D || rs.family == FAM_TB3D) && rs.frag.empty())
         mergeable[{rs.info.ndim, rs.info.dtype}].insert(2 * rs.info.radius + (rs.info.shape != STENCIL_STAR ? 1 : 0));
     }
+    // One step of 2D grids beside other classes: orders 1 and 2 walk, in one launch of
+    // all of them; a class of order 3 or 4 joins it only where it is small, as the
+    // merged walk is slow for its weights (us a step, merged / a kernel each, FP32 zero
+    // halo, from order 3 on: 16 grids of 128^2 of 2 / 3 / 8 stencils 12.9 / 11.1, 13.2 / 14.9,
+    // 15.1 / 28, two of 512^2 of 2 / 3 / 4 16.2 / 10.7, 17.0 / 14.6, 18.1 / 18.7, 16 of 256^2 of
+    // 2 / 4 / 8 21.8 / 11.8, 26.9 / 19.8, 34 / 29; orders 1 and 2: two of 512^2 of 3 stencils 9.0 / 14.3,
+    // eight of 2 11.3 / 12.6).
+    const int classes = (int)members.size();
     for (int32_t i = 0; i < count; ++i) {
       const Resolved& rs = plans[i]->rs;
       const int T = rs.tb_auto ? rs.time_block : 1;
@@ -230,7 +240,8 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
         std::vector<KArgs> as(T + 1);
         bool ok = true;
         for (int sz = 1; sz <= T && ok; ++sz) {
-          ks[sz] = plan_kernel(rs, buf0[i], buf1[i], &as[sz], sz, rs.pick_batch, columns[i], share[i]);
+          ks[sz] = plan_kernel(rs, buf0[i], buf1[i], &as[sz], sz, rs.pick_batch, columns[i], share[i],
+                               sz > 1 || classes > 3 ? classes : 1);
           ok = ks[sz].launch_batch && ks[sz].items >= 1;
         }
         if (ok) {
@@ -259,8 +270,10 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
       if (placed) continue;
       plain.emplace_back();
       plain.back().flops = rs.info.executed_flops_per_point;
-      plain.back().k = plan_kernel(rs, buf0[i], buf1[i], &plain.back().a, 1, nullptr, columns[i], share[i],
-                                   (int)mergeable[{rs.info.ndim, rs.info.dtype}].size());
+      int kinds = (int)mergeable[{rs.info.ndim, rs.info.dtype}].size();
+      if (rs.info.ndim == 2 && rs.info.radius >= 3) kinds = points[i] < 1.0e5 * classes ? classes : 1;
+      plain.back().k =
+          plan_kernel(rs, buf0[i], buf1[i], &plain.back().a, 1, nullptr, columns[i], share[i], kinds);
       if (rs.auto_rows) {
         // the gather that AUTO chose for the grid alone, or the outer products
         KArgs m;

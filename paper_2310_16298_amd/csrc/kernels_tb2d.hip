@@ -117,11 +117,15 @@ static bool any_tiles_better(const KArgs& a) {
 // of 256^2, stars r = 2..4 3.1 / 3.5, 3.7 / 4.7, 4.5 / 6.1, boxes r = 3, 4 6.1 / 7.1, 8.3 / 10.7;
 // 64 of 256^2 6.8 / 4.3, 11.7 / 6.3, 14.0 / 8.3, 21.3 / 13.3, 27.9 / 20.1; two FP64 ones of 512^2,
 // stars 2.7 / 3.4, 4.6 / 5.8, 4.4 / 6.8, order-2 box 3.3 / 4.1; eight 5.8 / 4.6, 9.6 / 7.3, 9.1 / 9.2,
-// 7.8 / 5.9; 50 FP32 order-4 stars of 96^2 4.1 / 4.6, four of 128^2 3.8 / 3.8).
+// 7.8 / 5.9; 50 FP32 order-4 stars of 96^2 4.1 / 4.6, four of 128^2 3.8 / 3.8).  Beside other
+// classes (a.kinds in all) their walks fill the chip, and a class cut in two is more
+// launches: 16 FP32 grids of 256^2 of 2 / 3 / 4 / 8 stencils 13.5 / 14.7, 17.2 / 16.4, 22.5 / 20.7, 30 /
+// 26.5; two of 512^2 10.5 / 12.4, 10.9 / 13.4 (3), 20.7 / 19.3 (8); the 120 mixed FP64 grids, 10 steps,
+// 606 / 565.
 template <typename T, int R, bool BOX>
 static bool lds_tiles_better_many(const KArgs& a) {
   const double total = (double)a.d0 * (double)a.d1 * 2048.0 / a.share;  // points of the class
-  if (total >= 1.6e6) return false;
+  if (a.kinds > 3 || total >= 1.6e6 || a.kinds * total >= 3.0e6) return false;
   if constexpr (sizeof(T) == 4) {
     if (R == 4) return a.d1 > 64 ? total >= (a.periodic ? 5.0e5 : 4.0e5) : !BOX && total >= 7.0e5;
     return a.d1 > 64 && total >= (R == 3 && !BOX && !a.periodic ? 5.0e5 : 7.0e5);

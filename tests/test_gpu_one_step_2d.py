@@ -132,3 +132,29 @@ def test_one_strip_of_many_rows_takes_the_walk():
     names = launched(torch, lambda: plan.run_steps(x, y, 2))
     plan.close()
     assert len(names) == 1 and "rs2d_kernel" in names[0], names
+
+
+# orders 3 and 4 join the merged walk only where their class is small
+@pytest.mark.parametrize("n,count,r,merged", [(64, 4, 3, True), (256, 16, 3, False), (256, 16, 1, True)])
+def test_two_stencils(n, count, r, merged):
+    torch = torch_cuda()
+    plans, b0, want = [], [], []
+    for order, shape in [(r, S), (r + 1, B)]:
+        c = inputs.coefficients(2, order, shape, seed=440 + order, dtype=np.float64)
+        plan = st.Plan((n, n), order, shape, c, boundary=Z, dtype=F, path=st.PATH_GATHER, time_block=1)
+        x = torch.from_numpy(_grid((n, n), 441 + order, F)).cuda()
+        plans += [plan] * count
+        b0 += [x.clone() for _ in range(count)]
+        want.append(plan.run_steps(x, torch.empty_like(x), 2).clone())
+    x0 = [b.clone() for b in b0]
+    b1 = [torch.full_like(b, float("nan")) for b in b0]
+    batch = st.Batch(plans, b0, b1)
+    names = launched(torch, lambda: batch.run_steps(1))
+    assert (len(names) == 1 and "rs2d_one_merged" in names[0]) == merged, names
+    for b, x in zip(b0, x0):
+        b.copy_(x)
+    out = (b0, b1)[batch.run_steps(2)]
+    torch.cuda.synchronize()
+    for k, got in enumerate(out):
+        assert torch.equal(got, want[k // count]), k
+    batch.close()

@@ -122,3 +122,28 @@ def test_ragged_order4_boxes(bc, dims, shift):
         edge = torch.cat([f[:32 + shift], f[32 + shift + a0.size:]])
         assert bool((edge == 7.5).all())
     plan.close()
+
+
+# beside more than three classes the walks fill the chip together
+@pytest.mark.parametrize("classes,tiles", [(2, True), (4, False)])
+def test_tiles_beside_other_classes(classes, tiles):
+    torch = torch_cuda()
+    plans, b0, want = [], [], []
+    for r, shape in [(3, st.STAR), (4, st.BOX), (4, st.STAR), (3, st.BOX)][:classes]:
+        c = inputs.coefficients(2, r, shape, seed=330 + r, dtype=np.float64)
+        plans += [st.Plan((250, 252), r, shape, c, boundary=P)] * 16
+        a0 = _grid((250, 252), 331 + r, st.F32)
+        b0 += [torch.from_numpy(a0).cuda() for _ in range(16)]
+        want.append(_run(torch, a0, r, shape, c, P, st.F32, 1, 6))
+    x0 = [b.clone() for b in b0]
+    b1 = [torch.full_like(b, float("nan")) for b in b0]
+    batch = st.Batch(plans, b0, b1)
+    names = launched(torch, lambda: batch.run_steps(6))
+    assert any("tb2d_dma_batch" in n for n in names) == tiles, names
+    for b, x in zip(b0, x0):
+        b.copy_(x)
+    out = (b0, b1)[batch.run_steps(6)]
+    torch.cuda.synchronize()
+    for k, got in enumerate(out):
+        assert torch.equal(got, want[k // 16]), k
+    batch.close()
