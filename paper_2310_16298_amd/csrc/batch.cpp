@@ -186,7 +186,7 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
     };
     std::vector<FragUse> frag_uses;
     std::vector<Plain> plain;  // grids of one step per launch
-    // columns per lane and shares of the waves of the gathers, by class
+    // columns per lane (3D: grids) and shares of the waves of the gathers, by class
     std::vector<int> columns(count, 0), share(count, 1);
     std::vector<double> points(count, 0.0);  // of the grid's class
     std::map<std::pair<Picker, int>, std::vector<int32_t>> members;
@@ -203,14 +203,12 @@ stencil_status_t stencil_batch_create(const stencil_plan_t* plans, void* const* 
         grids.push_back(&plans[i]->rs);
         bytes += (double)plans[i]->grid_bytes;
       }
-      // 2D: a grid's part of the class's bytes; 3D: an even part (whether small
-      // grids take a workgroup each goes by their number)
+      // a grid's part of the class's bytes; 3D also their number, by which small
+      // grids take a workgroup each
       const bool d2 = grids[0]->info.ndim == 2;
-      for (int32_t i : m.second)
-        share[i] = std::max(1, (int)(2048.0 * (d2 ? (double)plans[i]->grid_bytes / bytes : 1.0 / (double)grids.size())));
+      for (int32_t i : m.second) share[i] = std::max(1, (int)(2048.0 * (double)plans[i]->grid_bytes / bytes));
       for (int32_t i : m.second) points[i] = bytes / (grids[0]->info.dtype == STENCIL_F64 ? 8.0 : 4.0);
-      if (!d2) continue;
-      const int nc = rs2d_batch_cut(grids, share.data(), m.second.data());
+      const int nc = d2 ? rs2d_batch_cut(grids, share.data(), m.second.data()) : (int)grids.size();
       for (int32_t i : m.second) columns[i] = nc;
     }
     // one-step gathers of all taps merge by type and dimension

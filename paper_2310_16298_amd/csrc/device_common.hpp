@@ -39,7 +39,7 @@ struct KArgs {
   int32_t lcode0;       // line-cover kernel: slots 0..5, 5 bits each (bit 4: line along j, bits 0..3: index)
   int32_t lcode1;       // slots 6..8 in bits 0..14, number of lines in bits 27..30
   int32_t share;        // host only: 0 = alone in its launch, else the grid's share of the launch's waves
-  int32_t columns;      // host only: columns per lane of the batch's 2D gather class, 0 = free
+  int32_t columns;      // host only: in a batch, columns per lane of a 2D gather class, grids of a 3D one; 0 = free
   int32_t variant;      // merged batched kernels: 2 order + (box ? 1 : 0)
   int32_t kinds;        // host only: stencils whose one-step gathers merge in the launch, with this one
 };

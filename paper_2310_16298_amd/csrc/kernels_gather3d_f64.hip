@@ -10,7 +10,7 @@ template <int R, bool BOX>
 static Kernel pick_gather3d(KArgs& a, int32_t chunk) {
   if (chunk == 0) {
     const Rows3DCut c = rows3d_best(a, R, BOX, (int)sizeof(double));
-    if (a.share > 0 && whole3d_better(a, c, R, BOX, (int)sizeof(double))) {
+    if (a.share > 0 && whole3d_better(a, R, BOX, (int)sizeof(double))) {
       const Kernel whole = whole3d_kernel<double, R, BOX>(a);
       if (whole.launch_batch) return whole;
     }

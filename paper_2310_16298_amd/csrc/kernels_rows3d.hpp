@@ -435,14 +435,20 @@ inline double mfma3d_box_many_us(const RingLoad& l, int R) {
 // star 32^3 x 64 24 / 20, x 256 33 / 76; order-2 box 32^3 x 128 48 / 64, 24^3 x 128 45 / 36; order-3 box
 // 48^3 x 64 164 / 157, 32^3 x 256 236 / 281; FP64 27-point box 128^3 x 2 22 / 29, order-4 box 32^3 x 64 363 /
 // 188, x 256 650 / 742; 24^3 x 1024 2800 / 1556.
-// Beside other stencils of its type the rows also share a launch: there they are
-// taken below fifteen rounds of waves at any rate, as the ring would save a tenth to
-// a quarter and leave the merged kernel (120 mixed FP64 grids: 560 us, 640 with the
-// line at ten rounds, 861 with none).
+// Beside other stencils the ring's depth is hidden by their work, so a class of
+// one size has the rows up to nine tenths of its time only (us a step: four FP64 96^3
+// of the order-2 star and box 87 on rows, 62, with the 7-point star 109, 76; 40 mixed
+// grids, 15 steps, 461 at 1.0 and 0.9, 528 at 0.85).  Of mixed sizes the small grids fill the ring's
+// tiles badly (120 mixed FP64 grids, 10 steps, 572 at 1.0, 585 at 0.9).
+// The server's launches (columns = 0) follow one another on one stream: there the rows
+// share the merged one below fifteen rounds of waves at any rate (nine mixed requests,
+// an 80^3 star among them, 1370 us, 1470 with its ring launches).
 inline bool rows3d_better_many(const KArgs& a, const Rows3DCut& c, int R, bool box, int es) {
   const double width = c.NC == 1 ? 1.0 : c.NC == 2 ? 1.8 : 3.3;
-  if (a.kinds > 1 && 2048.0 / a.share * (double)c.waves * width < 30000.0) return true;
-  return rows3d_many_us(a, c, R, box, es) < ring3d_many_us(ring_load(a, R), R, box, es);
+  if (a.kinds > 1 && a.columns == 0 && 2048.0 / a.share * (double)c.waves * width < 30000.0) return true;
+  const double ring = ring3d_many_us(ring_load(a, R), R, box, es);
+  const bool one_size = a.columns * a.share <= 2048;
+  return rows3d_many_us(a, c, R, box, es) < (a.kinds > 1 && one_size ? 0.9 : 1.0) * ring;
 }
 
 // AUTO's FP32 boxes of order 3 and 4 among many: the n = 4 outer products, whose
@@ -510,11 +516,14 @@ inline bool rows3d_better(const KArgs& a, const Rows3DCut& c) {
 // order-3 star 64 grids 12.7 / 7.5, 150 12.8 / 15.2; 16^3 order-3 star, 128 grids
 // 22 / 19, 200 22 / 28; order-4 box 32 grids 250 / 30).  Beside other stencils the
 // rows share a launch.
-inline bool whole3d_better(const KArgs& a, const Rows3DCut& c, int R, bool box, int es) {
-  if (a.share <= 8 || !c.NC) return a.share <= 8;
-  if (a.kinds > 1) return false;
+inline bool whole3d_better(const KArgs& a, int R, bool box, int es) {
+  KArgs n = a;  // by the number of grids
+  if (a.columns > 0) n.share = std::max(1, 2048 / a.columns);
+  if (n.share <= 8) return true;
+  const Rows3DCut c = rows3d_best(n, R, box, es);
+  if (a.kinds > 1 || !c.NC) return false;
   const double points = (double)a.d0 * (double)a.d1 * (double)a.d2;
-  return whole3d_many_us(points, R, box, es) < rows3d_many_us(a, c, R, box, es);
+  return whole3d_many_us(points, R, box, es) < rows3d_many_us(n, c, R, box, es);
 }
 
 // AUTO's choice between the cut and the n = 4 outer products for FP32 boxes of

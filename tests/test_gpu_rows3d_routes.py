@@ -91,5 +91,15 @@ def test_two_stencils_share_the_rows(dtype):
     one = ((64, 64, 64), 1, S, P)
     names = _batch(torch, [one] * 16, dtype)
     assert len(names) == 1 and RING in names[0], names
-    names = _batch(torch, [one] * 8 + [((64, 64, 64), 2, S, Z)] * 8, dtype)
+    names = _batch(torch, [((32, 32, 32), 1, S, P)] * 8 + [((32, 32, 32), 2, S, Z)] * 8, dtype)
     assert len(names) == 1 and "rows3d_merged" in names[0], names
+    # large classes keep the ring beside each other
+    names = _batch(torch, [((128, 128, 128), r, S, P) for r in (1, 1, 2, 2)], dtype)
+    assert len(names) == 2 and all(RING in n for n in names), names
+
+
+# a class of grids of several sizes goes by its points, not by their number
+def test_sizes_of_a_class():
+    torch = torch_cuda()
+    names = _batch(torch, [((64, 64, 64), 2, B, Z)] + [((8, 8, 8), 2, B, Z)] * 30, D)
+    assert len(names) == 1 and "rows3d" in names[0], names
