@@ -41,7 +41,8 @@ struct KArgs {
   int32_t share;        // host only: 0 = alone in its launch, else the grid's share of the launch's waves
   int32_t columns;      // host only: in a batch, columns per lane of a 2D gather class, grids of a 3D one; 0 = free
   int32_t variant;      // merged batched kernels: 2 order + (box ? 1 : 0)
-  int32_t kinds;        // host only: stencils whose one-step gathers merge in the launch, with this one
+  int32_t kinds;        // host only: stencils beside which it runs, itself included: whose one-step gathers may
+                        // merge, or (2D time blocks and small classes) classes of the batch
 };
 
 // Pointer to data that no lane writes during a kernel (constant address
