@@ -447,7 +447,7 @@ inline bool rows3d_better_many(const KArgs& a, const Rows3DCut& c, int R, bool b
   const double width = c.NC == 1 ? 1.0 : c.NC == 2 ? 1.8 : 3.3;
   if (a.kinds > 1 && a.columns == 0 && 2048.0 / a.share * (double)c.waves * width < 30000.0) return true;
   const double ring = ring3d_many_us(ring_load(a, R), R, box, es);
-  const bool one_size = a.columns * a.share <= 2048;
+  const bool one_size = (int64_t)a.columns * a.share <= 2048;
   return rows3d_many_us(a, c, R, box, es) < (a.kinds > 1 && one_size ? 0.9 : 1.0) * ring;
 }
 
