@@ -380,7 +380,8 @@ struct RingLoad {
 };
 
 inline RingLoad ring_load(const KArgs& a, int R) {
-  const double grids = a.share > 0 ? 2048.0 / a.share : 1.0;
+  // the share is rounded down: 12 grids read back as 12.05, a round too many
+  const double grids = a.share > 0 ? std::max(1.0, std::floor(2048.0 / a.share)) : 1.0;
   RingLoad l;
   l.rounds = std::ceil(grids * (double)chunk3d_items(a) / 256.0);
   l.planes = grids * (double)a.nchunks * (a.chunk + 2 * R) * (double)(a.d1 * a.d2) / 2048.0e3;
@@ -394,7 +395,7 @@ inline double rows3d_many_us(const KArgs& a, const Rows3DCut& c, int R, bool box
   constexpr double k[2][2][5][2] = {
       {{{0, 0}, {4.4, 0.648}, {4.7, 0.834}, {4.8, 1.04}, {5.1, 1.26}}, {{0, 0}, {4.6, 0.803}, {5.8, 1.81}, {7.6, 3.9}}},
       {{{0, 0}, {4.5, 0.904}, {4.8, 1.227}, {4.8, 1.83}, {5.0, 2.2}}, {{0, 0}, {4.8, 1.084}, {6.5, 2.29}}}};
-  if (box && R == 4) return es == 4 ? 1.1 + 0.953 * c.time : 5.4 + 1.003 * c.time;
+  if (box && R == 4) return es == 4 ? 1.1 + (c.NC == 4 ? 1.16 : 0.953) * c.time : 5.4 + 1.003 * c.time;
   if (box && R == 3 && es == 8) return 2.5 + 1.028 * c.time;
   const double* f = k[es / 8][box ? 1 : 0][R];
   const double width = (c.NC == 1 ? 1.0 : c.NC == 2 ? 1.8 : 3.3) * c.J / 4.0;
@@ -454,13 +455,14 @@ inline bool rows3d_better_many(const KArgs& a, const Rows3DCut& c, int R, bool b
 // AUTO's FP32 boxes of order 3 and 4 among many: the n = 4 outer products, whose
 // rate at a full chip the gathers do not reach (us a step, best gather / outer products: order 4
 // 256 grids of 32^3 442 / 339, 64 of 64^3 525 / 390, 128 of 48^3 650 / 506, 128 of 32^3 253 / 205, order 3 236 / 207,
-// 257 / 226; not 64 of 32^3, order 4 148 / 197, order 3 72 / 101).
+// 257 / 226; eight and twelve of 128^3, order 4, 443 / 393, 672 / 558, four of 160^3 645 / 545; not 64 of
+// 32^3, order 4 149 / 195, order 3 73 / 101, nor six of 128^3 338 / 387).
 inline bool outer_products_better_many(const KArgs& a, int R) {
   const Rows3DCut c = rows3d_best(a, R, true, 4);
   if (!dma3d_ok<float>(a) || a.share <= 0 || c.NC == 0) return false;
   const RingLoad l = ring_load(a, R);
   const double gather = std::min(rows3d_many_us(a, c, R, true, 4), ring3d_many_us(l, R, true, 4));
-  return mfma3d_box_many_us(l, R) < (R == 4 ? 0.95 : 1.0) * gather;
+  return mfma3d_box_many_us(l, R) < gather;
 }
 
 // A grid alone of up to 32 MB, us a step, ring / rows: on the rows, except where their

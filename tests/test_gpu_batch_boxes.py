@@ -21,6 +21,7 @@ pytestmark = pytest.mark.gpu
     (4, (32, 32, 32), 256, st.PATH_GATHER, False), (3, (32, 32, 32), 256, st.PATH_AUTO, True),
     (3, (20, 44, 48), 16, st.PATH_AUTO, False), (4, (39, 41, 64), 64, st.PATH_AUTO, False),
     (4, (31, 63, 64), 64, st.PATH_AUTO, True),
+    (4, (127, 128, 128), 12, st.PATH_AUTO, True),
     (4, (33, 33, 33), 256, st.PATH_AUTO, False)])
 def test_boxes_among_many(r, dims, count, path, outer, bc):
     torch = torch_cuda()
